@@ -413,6 +413,9 @@ int rtssa_debug_neglog(const uint64_t* m, double* out, uint8_t* slow, int64_t co
 double rtssa_debug_neglog_host(uint64_t m, int32_t force_accurate, int32_t* slow);
 /* The fast phase's double-double approximation yh + yl of -ln u (m < 2^53 - 1). */
 void rtssa_debug_neglog_fast_host(uint64_t m, double* yh, double* yl);
+/* The quick phase alone: 1 and *y = RN(-ln u) where it certifies its rounding,
+ * else 0. */
+int32_t rtssa_debug_neglog_quick_host(uint64_t m, double* y);
 /* The selection step (Eq. 25) and the near-tie rule of one mapping, run by
  * the same device functions as the simulation kernels on given values:
  * v device float64 [count][M] (no NaN; +inf allowed); per row r:

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(L, group_min_waves(S, SCHED)) void rt_group_kernel(
     // sets bits between barriers 1 and 2; every thread reads and clears its
     // own word in the next pass, before the next barrier 1.
     uint32_t* stale_w = nk + ((C.max_M + 3) & ~3);                   // [L]
-    uint32_t* sc = sh.log_scratch[wave];
+    const rt_log_ctx<rt_log_const_tab> sc{{}, sh.log_scratch[wave]};
 
     // channel state: slot s of thread tid is channel tid + s L; slots past M
     // are frozen channels (a = 0) and never win
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(L, group_min_waves(S, SCHED)) void rt_group_kernel(
             if (wave == (owner_lane >> 6)) {
                 nm = nk[mu];
                 E = rt_exp1_uniform(key0, key1, traj, net_id, (uint32_t)mu, nm + 1u,
-                                    &ws->slow_logs, sc);
+                                    &ws->slow_logs, sc.sc);
                 if (d1 == 0.0 && tid == owner_lane) {
                     // a zero gap: was it clamped from a negative raw gap?
                     const int sm = mu >> LOG2L;

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
     double* const pinv = g2_lds + L * S;                          // [L S] 1/a_k
     const int Npad = (C.max_N + 3) & ~3;
     int32_t* const Xb = (int32_t*)(g2_lds + 2 * L * S);           // [2][Npad]
-    uint32_t* sc = sh.log_scratch[wave];
+    const rt_log_ctx<rt_log_const_tab> sc{{}, sh.log_scratch[wave]};
 
     double T[S], P[S], En[S];
     uint32_t nk[S];

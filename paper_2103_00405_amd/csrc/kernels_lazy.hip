@@ -350,7 +350,8 @@ __global__ __launch_bounds__(64) void rt_lazy_kernel(rt_class_dev C, rt_lazy_rec
             const rt_u4 w = rt_philox4x32_10(rt_u4{0u, (uint32_t)k, traj, net_id}, key0, key1);
             wnext[k] = ((unsigned long long)w.w << 32) | w.z;
             const double P = rt_neglog_wave((((uint64_t)w.y << 32) | w.x) >> 11, false,
-                                            &ws->slow_logs, log_scratch);
+                                            &ws->slow_logs,
+                                            rt_log_ctx<rt_log_const_tab>{{}, log_scratch});
             const double a = rt_propensity_mem(react[k], cc[k], X);
             bool cl;
             leaves[k] = lazy_tau(0.0, 0.0, P, a, &cl);

@@ -91,13 +91,14 @@ __global__ __launch_bounds__(256) void rt_debug_neglog_kernel(const uint64_t* m,
                                                                uint8_t* slow, int64_t count,
                                                                int force)
 {
-    __shared__ uint32_t log_scratch[4][RT_LOG_SCRATCH];
+    __shared__ rt_log_lds<4> log_lds;
     __shared__ unsigned long long slow_count[256];
+    const auto lc = log_lds.init();
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= count) return;
     slow_count[threadIdx.x] = 0ull;
     out[i] = rt_neglog_wave(m[i], force != 0, &slow_count[threadIdx.x],
-                            log_scratch[threadIdx.x >> 6]);
+                            lc);
     if (slow) slow[i] = slow_count[threadIdx.x] ? 1 : 0;
 }
 

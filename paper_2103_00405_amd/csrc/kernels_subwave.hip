@@ -52,8 +52,8 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
     const int tid = threadIdx.x, li = tid % L, lane = tid & 63;
     const unsigned long long gmask = kGroupBits << (lane - li);
     extern __shared__ int32_t dyn_lds[];
-    __shared__ uint32_t log_scratch[kBlock / 64][RT_LOG_SCRATCH];
-    uint32_t* sc = log_scratch[tid >> 6];
+    __shared__ rt_log_lds<kBlock / 64> log_lds;
+    const auto sc = log_lds.init();
     constexpr int LOG2L = __builtin_ctz(L);
     const int NP = (C.max_N + 3) & ~3, MP = (C.max_M + 3) & ~3;
     int32_t* X = dyn_lds + (tid / L) * (NP + L + MP);   // [N] species counts

@@ -110,8 +110,8 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
     // first; alone on the device every wavefront has the same priority.
     __builtin_amdgcn_s_setprio(3);
     const uint32_t key0 = ws->key0, key1 = ws->key1;
-    __shared__ uint32_t log_scratch[4][RT_LOG_SCRATCH];     // one slice per wave
-    uint32_t* sc = log_scratch[threadIdx.x >> 6];
+    __shared__ rt_log_lds<4> log_lds;
+    const auto sc = log_lds.init();
     // per-lane buffer of one 64-byte line of sample output: a lane's sample
     // row is written a few bytes at a time, at its own event times; collecting
     // the words of a line and storing them together lets the L2 write each

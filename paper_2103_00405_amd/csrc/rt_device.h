@@ -113,78 +113,123 @@ __device__ __forceinline__ int rt_find_item(rt_cptr<int64_t> unit_start, int cou
     return lo;
 }
 
-// RN(-ln u) for the wave's active lanes.  The fast phase runs in every lane;
-// lanes whose rounding it cannot certify (about one draw in 2^17) take turns
-// on the wave's LDS slice sc (RT_LOG_SCRATCH words) for the accurate phase;
-// each such lane adds one to the device counter *slow, or, with slow = NULL,
-// sets *took_slow instead (for a draw that may be discarded and counted only
-// once it is used).
-__device__ __forceinline__ double rt_neglog_wave(uint64_t m, bool force_accurate,
-                                                 unsigned long long* slow, uint32_t* sc,
-                                                 bool* took_slow = nullptr)
+// Where a kernel's per-lane logarithms find the quick phase's table.  The
+// thread and sub-wave kernels keep a copy in LDS (4 KiB per workgroup): its
+// reads are counted apart from the global loads in flight, and 64 lanes'
+// entries come faster than from the vector L1.  Kernels whose LDS bounds the
+// network size read the constant table itself.
+struct rt_log_lds_tab {
+    const rt_logq* tab;
+    __device__ __forceinline__ rt_logq operator()(uint32_t i) const { return tab[i]; }
+};
+struct rt_log_const_tab {
+    __device__ __forceinline__ rt_logq operator()(uint32_t i) const { return rt_logq_const(i); }
+};
+
+template <class Tab>
+struct rt_log_ctx {
+    Tab tab;
+    uint32_t* sc;       // RT_LOG_SCRATCH words of LDS for the accurate phase
+};
+
+template <int WAVES>
+struct rt_log_lds {
+    rt_logq tab[RT_LOGQ_N];
+    uint32_t scratch[WAVES][RT_LOG_SCRATCH];
+
+    // Every thread of the workgroup calls this once before the first draw.
+    __device__ __forceinline__ rt_log_ctx<rt_log_lds_tab> init()
+    {
+        for (int i = (int)threadIdx.x; i < RT_LOGQ_N; i += (int)blockDim.x)
+            tab[i] = rt_logq_const((uint32_t)i);
+        __syncthreads();
+        return {{tab}, scratch[threadIdx.x >> 6]};
+    }
+};
+
+// The draws the quick phase left open (about one in 2^12.5): the fast phase,
+// and for those it cannot certify either (one in 2^20) the accurate phase, in
+// which the lanes take turns on the wave's LDS slice.  Called with the lanes
+// that are open in this wavefront; true in the lanes that took the accurate
+// phase.
+__device__ __forceinline__ bool rt_neglog_open(uint64_t m, bool force_accurate, uint32_t* sc,
+                                               double& y)
 {
     int e, i;
     double z;
     rt_neglog_reduce(m, e, i, z);
-    double y = 0.0;
     bool need = m != 0x1FFFFFFFFFFFFFull;                     // u = 1 gives +0
+    y = 0.0;
     if (need && !force_accurate) {
         double yh, yl;
         rt_neglog_fast(e, i, z, yh, yl);
         y = yh;
         need = !rt_rounding_certain(yh, yl);
     }
-    if (took_slow) *took_slow = need;
     unsigned long long pending = __ballot(need);
     if (__builtin_expect(pending != 0ull, 0)) {
         const int me = (int)(threadIdx.x & 63u);
         while (pending) {
             const int lane = __ffsll((long long)pending) - 1;
-            if (lane == me) {
-                y = rt_neglog_accurate(e, i, z, sc);
-                if (slow) atomicAdd(slow, 1ull);
-            }
+            if (lane == me) y = rt_neglog_accurate(e, i, z, sc);
             pending &= pending - 1ull;
+        }
+    }
+    return need;
+}
+
+// RN(-ln u) for the wave's active lanes; each lane that needs the accurate
+// phase adds one to the device counter *slow, or, with slow = NULL, sets
+// *took_slow instead (for a draw that may be discarded and counted only once
+// it is used).
+template <class Tab>
+__device__ __forceinline__ double rt_neglog_wave(uint64_t m, bool force_accurate,
+                                                 unsigned long long* slow,
+                                                 const rt_log_ctx<Tab>& lc,
+                                                 bool* took_slow = nullptr)
+{
+    double y;
+    const bool open = !rt_neglog_quick(m, lc.tab, y) || force_accurate;
+    if (took_slow) *took_slow = false;
+    if (__builtin_expect(__ballot(open) != 0ull, 0)) {
+        if (open) {
+            const bool acc = rt_neglog_open(m, force_accurate, lc.sc, y);
+            if (took_slow) *took_slow = acc;
+            if (slow && acc) atomicAdd(slow, 1ull);
         }
     }
     return y;
 }
 
 // RN(-ln u) when every active lane holds the same m (a draw computed by a
-// whole wavefront for one channel): the accurate phase, when needed, runs
-// once in the first active lane and its result is broadcast; *slow counts
-// one per draw.
+// whole wavefront for one channel).  The table entry is a scalar load, which
+// does not wait for the vector loads in flight; past the quick phase the value
+// is computed in the first active lane and broadcast; *slow counts one per
+// accurate phase.
 __device__ __forceinline__ double rt_neglog_uniform(uint64_t m, unsigned long long* slow,
                                                     uint32_t* sc)
 {
-    int e, i;
-    double z;
-    rt_neglog_reduce(m, e, i, z);
-    double y = 0.0;
-    bool need = m != 0x1FFFFFFFFFFFFFull;                     // u = 1 gives +0
-    if (need) {
-        double yh, yl;
-        rt_neglog_fast(e, i, z, yh, yl);
-        y = yh;
-        need = !rt_rounding_certain(yh, yl);
-    }
-    if (__builtin_expect(__ballot(need) != 0ull, 0)) {
+    double y;
+    const bool open = !rt_neglog_quick(
+        m, [](uint32_t i) { return rt_logq_const(__builtin_amdgcn_readfirstlane(i)); }, y);
+    if (__builtin_expect(__ballot(open) != 0ull, 0)) {
         const unsigned long long active = __ballot(true);
         const int first = __ffsll((long long)active) - 1;
         if ((int)(threadIdx.x & 63u) == first) {
-            y = rt_neglog_accurate(e, i, z, sc);
-            atomicAdd(slow, 1ull);
+            if (rt_neglog_open(m, false, sc, y)) atomicAdd(slow, 1ull);
         }
         y = __shfl(y, first, 64);
     }
     return y;
 }
 
+template <class Tab>
 __device__ __forceinline__ double rt_exp1_wave(uint32_t k0, uint32_t k1, uint32_t traj,
                                                uint32_t net, uint32_t k, uint32_t n,
-                                               unsigned long long* slow, uint32_t* sc)
+                                               unsigned long long* slow,
+                                               const rt_log_ctx<Tab>& lc)
 {
-    return rt_neglog_wave(rt_draw_m53(k0, k1, traj, net, k, n), false, slow, sc);
+    return rt_neglog_wave(rt_draw_m53(k0, k1, traj, net, k, n), false, slow, lc);
 }
 
 // E for channel k at firing index n, computed by every active lane alike.
