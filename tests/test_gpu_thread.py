@@ -87,6 +87,30 @@ def test_birth_death_gradient_config_bit_exact():
     _assert_same(g, ref)
 
 
+@pytest.mark.parametrize("R,block,grid", [(1, 64, 1), (65, 64, 1), (257, 256, 1), (1999, 64, 2),
+                                          (5003, 256, 3), (3000, 128, 0)])
+def test_every_trajectory_is_taken_once(R, block, grid):
+    """Lanes take trajectories from ranges their wavefront reserves: fewer
+    trajectories than lanes, many more than a small grid holds, odd counts;
+    each trajectory has its own initial count, so a trajectory taken twice,
+    left out or counted twice shows."""
+    spec = W.birth_death(20.0, 2.0)
+    x0 = np.random.default_rng(R).integers(0, 40, size=(R, 1)).astype(np.int32)
+    api = _api()
+    g = api.simulate(api.Network(spec), x0, 1.0, [0.5, 1.0], R, seed=9, block=block, grid=grid,
+                     with_hash=True)
+    ref = [oracle.simulate(spec, x0[r], 1.0, [0.5, 1.0], 9, 1, traj_offset=r) for r in range(R)]
+    for key, view in (("samples", None), ("n", np.uint32), ("T", np.uint64), ("x_final", None),
+                      ("status", None), ("seq_hash", np.uint64)):
+        got = _np(g[key])
+        want = np.concatenate([o[key] for o in ref])
+        if view is not None:
+            got, want = got.view(view), want.view(view)
+        assert np.array_equal(got, want), key
+    assert g["stats"]["firings"] == sum(o["stats"]["firings"] for o in ref)
+    assert sum(g["stats"]["status_count"]) == R
+
+
 def test_edge_cases():
     # empty network: every trajectory is absorbed at t = 0
     spec0 = W.from_reactions(2, [])
