@@ -416,6 +416,9 @@ void rtssa_debug_neglog_fast_host(uint64_t m, double* yh, double* yl);
 /* The quick phase alone: 1 and *y = RN(-ln u) where it certifies its rounding,
  * else 0. */
 int32_t rtssa_debug_neglog_quick_host(uint64_t m, double* y);
+/* out[i] = RN(1 / a[i]) as the kernels compute it (device arrays; a and 1 / a
+ * normal). */
+int rtssa_debug_recip(const double* a, double* out, int64_t count, rtssa_stream_t stream);
 /* The selection step (Eq. 25) and the near-tie rule of one mapping, run by
  * the same device functions as the simulation kernels on given values:
  * v device float64 [count][M] (no NaN; +inf allowed); per row r:

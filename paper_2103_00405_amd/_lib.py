@@ -69,6 +69,7 @@ SIGNATURES = {
     "rtssa_autotune": (C.c_int, [C.POINTER(BatchItem), i32, i32, C.c_char_p, vp]),
     "rtssa_debug_neglog": (C.c_int, [vp, vp, vp, i64, i32, vp]),
     "rtssa_debug_neglog_host": (f64, [u64, i32, C.POINTER(i32)]),
+    "rtssa_debug_recip": (i32, [vp, vp, i64, vp]),
     "rtssa_debug_neglog_quick_host": (i32, [u64, C.POINTER(f64)]),
     "rtssa_debug_neglog_fast_host": (None, [u64, C.POINTER(f64), C.POINTER(f64)]),
     "rtssa_debug_philox": (C.c_int, [vp, u32, u32, vp, i64, vp]),

@@ -459,6 +459,13 @@ extern "C" int rtssa_debug_philox(const uint32_t* ctr, uint32_t key0, uint32_t k
     return rt_launch_debug_philox(ctr, key0, key1, out, count, (hipStream_t)stream);
 }
 
+extern "C" int rtssa_debug_recip(const double* a, double* out, int64_t count,
+                                 rtssa_stream_t stream)
+{
+    if (count < 0 || (count > 0 && (!a || !out))) return rt_fail(RTSSA_E_INVALID, "bad arguments");
+    return rt_launch_debug_recip(a, out, count, (hipStream_t)stream);
+}
+
 extern "C" int rtssa_debug_select(const double* v, int32_t M, int64_t count, int32_t mapping,
                                   int32_t lanes, int32_t* mu, double* v1, double* v2,
                                   uint8_t* near, rtssa_stream_t stream)

@@ -16,10 +16,7 @@ Tables written here:
   THIRD_H, THIRD_L 1/3 as a double-double
 First (quick) phase, a table of 256 pairs for the top 8 mantissa bits of f in
 [1, 2), with -ln u = -e ln 2 + ln r - ln(1 + z) and r in [1/2, 1]:
-  LOGQ[2 i], LOGQ[2 i + 1]   (H, L): H is ln r_i to a multiple of 2^-46, L the
-                   rest to about 31 bits; bits 12..20 of L's low word hold
-                   the high word of r_i (9 significant bits) xor that of 1.0,
-                   so that one 16-byte read gives H, L and r_i
+  LOGQ[3 i ..]     (H, L, r_i): H is ln r_i to a multiple of 2^-46, L the rest
   QLN2_H, QLN2_L   ln 2 in the same form: at u just below 1 (r = 1/2, e = -1)
                    the table's terms cancel to exactly 0
   LOGQ_C[j]        coefficients of (ln(1+z) - z + z^2/2) / z^3 to degree 5 on
@@ -31,7 +28,6 @@ digits; no other source is consulted.  Run: python gen_log_tables.py > log_table
 from decimal import Decimal, getcontext
 from fractions import Fraction
 import math
-import struct
 import sys
 
 getcontext().prec = 120
@@ -72,18 +68,6 @@ def fix(x: Decimal) -> list:
 
 QBITS = 8            # index bits of the quick phase's table
 QGRID = 46           # H is a multiple of 2^-QGRID
-QMASK = 0x001FF000   # bits of L's low word that hold r
-
-
-def quick_low(L: Decimal, code: int) -> float:
-    """The double nearest L (in magnitude, from below) whose low word carries
-    `code` in the bits of QMASK and nothing under them."""
-    if L == 0:
-        assert code == 0
-        return 0.0
-    b = struct.unpack("<Q", struct.pack("<d", float(L)))[0]
-    b = (b & ~((QMASK << 1) & 0xFFFFFFFF | 0xFFFFF)) | code
-    return struct.unpack("<d", struct.pack("<Q", b))[0]
 
 
 def quick_tables():
@@ -95,15 +79,12 @@ def quick_tables():
         ri = Fraction(1) if i == 0 else round_sig(2 / (lo + hi), 9)
         zmax = max(abs(lo * ri - 1), abs(hi * ri - 1))
         assert Fraction(1, 2) <= ri <= 1 and zmax <= Fraction(1, 256), (i, float(zmax))
-        code = (struct.unpack("<Q", struct.pack("<d", float(ri)))[0] >> 32) ^ 0x3FF00000
-        assert code & ~QMASK == 0
         ln_r = dec(ri).ln()
         H = Fraction(int((ln_r * Decimal(2 ** QGRID)).to_integral_value())) / grid
         L = ln_r - dec(H)
         r.append(ri)
-        hl.append((float(H), quick_low(L, code)))
+        hl.append((float(H), float(L)))
         assert Fraction(hl[-1][0]) == H
-        assert abs(Decimal(hl[-1][1]) - L) <= Decimal(2) ** -76, i
     assert r[n - 1] == Fraction(1, 2)
     ln2_h, ln2_l = -hl[n - 1][0], -hl[n - 1][1]
     # the sum h - ln(1 + z), h = -e ln2_h + H: h is 0 or its exponent is not
@@ -123,7 +104,7 @@ def quick_tables():
     c[4] += c[6] * a2 * Fraction(48, 32)
     c[2] -= c[6] * a2 ** 2 * Fraction(18, 32)
     c[0] += c[6] * a2 ** 3 * Fraction(1, 32)
-    return hl, ln2_h, ln2_l, [float(x) for x in c[:6]]
+    return [(h, l, float(x)) for (h, l), x in zip(hl, r)], ln2_h, ln2_l, [float(x) for x in c[:6]]
 
 
 def hexd(x: float) -> str:
@@ -179,12 +160,12 @@ def main(out):
     arr_d("RT_RTAB", rtab)
     arr_d("RT_LNR_H", lnr_h)
     arr_d("RT_LNR_L", lnr_l)
-    hl, qln2_h, qln2_l, qc = quick_tables()
-    w("#define RT_LOGQ_BITS %d\n#define RT_LOGQ_RMASK 0x%08xu\n" % (QBITS, QMASK))
+    rows, qln2_h, qln2_l, qc = quick_tables()
+    w("#define RT_LOGQ_BITS %d\n" % QBITS)
     w("#define RT_QLN2_H %s\n#define RT_QLN2_L %s\n" % (hexd(qln2_h), hexd(qln2_l)))
     for j, v in enumerate(qc):
         w("#define RT_LOGQ_C%d %s\n" % (j, hexd(v)))
-    arr_d("RT_LOGQ", [x for pair in hl for x in pair])
+    arr_d("RT_LOGQ", [x for row in rows for x in row])
     arr_fix("RT_LNR_FIX", lnr_fix)
     w("RT_LOG_CONST uint32_t RT_LN2_FIX[%d] = {" % LIMBS + ", ".join("0x%08xu" % v for v in fix(ln2)) + "};\n")
     arr_fix("RT_INVK_FIX", [fix(Decimal(1) / Decimal(j + 1)) for j in range(KMAX + 1)])

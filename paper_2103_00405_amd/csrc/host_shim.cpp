@@ -28,7 +28,7 @@ extern "C" void rtssa_debug_neglog_fast_host(uint64_t m, double* yh, double* yl)
 // The quick phase alone: its value, and whether it certifies the rounding.
 extern "C" int32_t rtssa_debug_neglog_quick_host(uint64_t m, double* y)
 {
-    return rt_neglog_quick(m, rt_logq_const, *y) ? 1 : 0;
+    return rt_neglog_quick((uint32_t)(m >> 32), (uint32_t)m, rt_logq_const, *y) ? 1 : 0;
 }
 
 extern "C" void rtssa_debug_philox_host(const uint32_t ctr[4], uint32_t key0, uint32_t key1,

@@ -176,6 +176,7 @@ int rt_launch_debug_neglog(const uint64_t* m, double* out, uint8_t* slow, int64_
 int rt_launch_debug_select(const double* v, int32_t M, int64_t count, int32_t mapping,
                            int32_t lanes, int32_t* mu, double* v1, double* v2, uint8_t* near,
                            hipStream_t stream);
+int rt_launch_debug_recip(const double* a, double* out, int64_t count, hipStream_t stream);
 int rt_launch_debug_philox(const uint32_t* ctr, uint32_t k0, uint32_t k1, uint32_t* out,
                            int64_t count, hipStream_t stream);
 int rt_thread_supported(int M, int N);

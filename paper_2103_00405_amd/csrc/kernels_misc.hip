@@ -115,6 +115,12 @@ __global__ void rt_debug_philox_kernel(const uint32_t* ctr, uint32_t k0, uint32_
     out[4 * i + 3] = w.w;
 }
 
+__global__ void rt_debug_recip_kernel(const double* a, double* out, int64_t count)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < count) out[i] = rt_recip(a[i]);
+}
+
 // ---- the selection step (Eq. 25) and near-tie rule of each mapping, on
 // rows of given values (test hook); the same device functions as the kernels
 __device__ __forceinline__ void debug_sel_store(int64_t r, const rt_min2& v, int32_t* mu,
@@ -297,5 +303,13 @@ int rt_launch_debug_philox(const uint32_t* ctr, uint32_t k0, uint32_t k1, uint32
     if (count <= 0) return RTSSA_OK;
     hipLaunchKernelGGL(rt_debug_philox_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
                        stream, ctr, k0, k1, out, count);
+    return hipGetLastError() == hipSuccess ? RTSSA_OK : rt_fail(RTSSA_E_HIP, "launch failed");
+}
+
+int rt_launch_debug_recip(const double* a, double* out, int64_t count, hipStream_t stream)
+{
+    if (count <= 0) return RTSSA_OK;
+    hipLaunchKernelGGL(rt_debug_recip_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
+                       stream, a, out, count);
     return hipGetLastError() == hipSuccess ? RTSSA_OK : rt_fail(RTSSA_E_HIP, "launch failed");
 }

@@ -23,32 +23,80 @@
 
 namespace {
 
-// X[j] for a wave-uniform j (a species index of the network): a switch
-// becomes scalar branches, so X stays in registers instead of being copied
-// to scratch memory for an indexed load.
-template <int NT>
-__device__ __forceinline__ int32_t pick(const int32_t (&X)[NT], int j)
+// fn(x[j]) for a wave-uniform j (a species index of the network): a switch
+// becomes scalar branches, so x stays in registers instead of being copied
+// to scratch memory for an indexed load, and each branch works on its own
+// register rather than on a copy of it.
+template <int NT, class F>
+__device__ __forceinline__ void with_species(const double (&x)[NT], int j, F fn)
 {
     switch (j) {
-        case 1: if constexpr (NT > 1) return X[1]; break;
-        case 2: if constexpr (NT > 2) return X[2]; break;
-        case 3: if constexpr (NT > 3) return X[3]; break;
-        case 4: if constexpr (NT > 4) return X[4]; break;
-        case 5: if constexpr (NT > 5) return X[5]; break;
-        case 6: if constexpr (NT > 6) return X[6]; break;
-        case 7: if constexpr (NT > 7) return X[7]; break;
+        case 1: if constexpr (NT > 1) { fn(x[1]); return; } break;
+        case 2: if constexpr (NT > 2) { fn(x[2]); return; } break;
+        case 3: if constexpr (NT > 3) { fn(x[3]); return; } break;
+        case 4: if constexpr (NT > 4) { fn(x[4]); return; } break;
+        case 5: if constexpr (NT > 5) { fn(x[5]); return; } break;
+        case 6: if constexpr (NT > 6) { fn(x[6]); return; } break;
+        case 7: if constexpr (NT > 7) { fn(x[7]); return; } break;
         default: break;
     }
-    return X[0];
+    fn(x[0]);
 }
 
-// a_k of Eq. 1-2 with the reaction kind fixed per channel (uniform branch)
-// and X in registers.
-template <int NT>
-__device__ __forceinline__ double propensity(int kind, int s0, int s1, double c,
-                                             const int32_t (&X)[NT])
+// The rate constant as propensities() uses it: halved for a homodimer
+// (exact: c is 0 or at least 1e-280).
+__device__ __forceinline__ double kernel_rate(int kind, double c)
 {
-    return rt_propensity(kind, s0, s1, c, [&](int j) { return pick<NT>(X, j); });
+    return kind == RT_H_PAIR ? 0.5 * c : c;
+}
+
+// a_k = RN(c_k RN(h_k)) of Eq. 1-2 for every channel, the kinds wave-uniform
+// and X in registers.  Counts are below 2^31, so a product of two is exact
+// before its one rounding: RN(X_i X_j) is the binary64 product, and a
+// homodimer's 2 RN(h) = RN(X^2 - X) one fma (+0 for X = 0 and 1), its factor
+// 1/2 in the rate; no 64-bit integer product and one conversion per species.
+template <int MT, int NT>
+__device__ __forceinline__ void propensities(const int (&kind)[MT], const int (&s0)[MT],
+                                             const int (&s1)[MT], const double (&c)[MT],
+                                             const int32_t (&X)[NT], double (&a)[MT])
+{
+    double x[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) x[j] = (double)(uint32_t)X[j];
+#pragma unroll
+    for (int k = 0; k < MT; ++k) {
+        if (kind[k] == RT_H_ZERO) {
+            a[k] = c[k];
+        } else if (kind[k] == RT_H_ONE) {
+            with_species<NT>(x, s0[k], [&](double u) { a[k] = c[k] * u; });
+        } else if (kind[k] == RT_H_PAIR) {
+            with_species<NT>(x, s0[k], [&](double u) { a[k] = c[k] * fma(u, u, -u); });
+        } else if constexpr (NT == 2) {
+            a[k] = c[k] * (x[0] * x[1]);
+        } else {
+            double u = 0.0;
+            with_species<NT>(x, s0[k], [&](double v) { u = v; });
+            with_species<NT>(x, s1[k], [&](double v) { a[k] = c[k] * (u * v); });
+        }
+    }
+}
+
+// The two smallest of MT binary32 values; a NaN makes them equal.
+template <int MT>
+__device__ __forceinline__ void rt_two_smallest(const float (&v)[MT], float& g1, float& g2)
+{
+    g1 = v[0];
+    g2 = __builtin_inff();
+    if constexpr (MT == 3) {
+        g1 = fminf(fminf(v[0], v[1]), v[2]);
+        g2 = __builtin_amdgcn_fmed3f(v[0], v[1], v[2]);
+    } else {
+#pragma unroll
+        for (int k = 1; k < MT; ++k) {
+            g2 = __builtin_amdgcn_fmed3f(g1, g2, v[k]);
+            g1 = fminf(g1, v[k]);
+        }
+    }
 }
 
 // Collects one lane's writes to one 64-byte line in its LDS buffer and
@@ -200,6 +248,10 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
     __shared__ rt_wave_share wave_shares[4];
     rt_wave_share& share = wave_shares[threadIdx.x >> 6];
     share.clear();
+    // firing counts n_k of the lane's trajectory: the count behind the next draw
+    // comes from one LDS atomic instead of selects over every channel's register
+    __shared__ uint32_t counts[MT][256];
+    uint32_t* const cnt = &counts[0][threadIdx.x];
 
     int item = C.exclusive ? -1 : 0;
     bool first = true;
@@ -231,7 +283,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                 kind[k] = (int)((uint32_t)rr.x >> 29);
                 s0[k] = rr.x & RT_SPECIES_MASK;
                 s1[k] = rr.y;
-                c[k] = rt_const(net.c)[k];
+                c[k] = kernel_rate(kind[k], rt_const(net.c)[k]);
             } else {
                 kind[k] = RT_H_ZERO; s0[k] = 0; s1[k] = 0; c[k] = 0.0;   // dead padding channel
             }
@@ -247,16 +299,28 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
         const double t_end = it->t_end;
         const uint32_t net_id = it->net_id, traj_offset = it->traj_offset;
         const bool want_hash = it->seq_hash != nullptr;
+        const uint32_t net_k1 = net_id ^ key1;
+        // counts up to here are safe from any jump's increase
+        int32_t up = 0;
+#pragma unroll
+        for (int k = 0; k < MT; ++k)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) up = max(up, nu[k][j]);
+        const uint32_t x_safe = 0x7FFFFFFFu - (uint32_t)up;
 
         // ---- trajectory state
         int32_t X[NT];
-        double T[MT], Pk[MT], a[MT], inv[MT];
-        uint32_t n[MT];
+        double T[MT], Pk[MT], a[MT];
+        rt_traj_words tw{0u, 0u};
 #pragma unroll
         for (int j = 0; j < NT; ++j) X[j] = 0;
 #pragma unroll
-        for (int k = 0; k < MT; ++k) { T[k] = 0.0; Pk[k] = 0.0; a[k] = 0.0; inv[k] = 0.0; n[k] = 0; }
+        for (int k = 0; k < MT; ++k) { T[k] = 0.0; Pk[k] = 0.0; a[k] = 0.0; }
         double t = 0.0, s_next = 0.0;
+        // the earliest of the next sample point, the next rate breakpoint and
+        // t_end: a firing past it needs the rare branch (so does every pass of
+        // a lane without a trajectory in progress, which holds -1 here)
+        double t_stop = -1.0;
         // SCHED: the rates in force for this lane's trajectory, the index of
         // the next breakpoint and its time
         double cl[MT];
@@ -276,43 +340,83 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
             for (int j = 0; j < NT; ++j)
                 if (j < N) lw.put(dst + j * it->ss_n, invalid ? -1 : X[j]);
         };
+        auto refresh = [&]() {
+            if constexpr (SCHED) propensities<MT, NT>(kind, s0, s1, cl, X, a);
+            else propensities<MT, NT>(kind, s0, s1, c, X, a);
+        };
 
-        // Each pass is one firing of every active lane.  The common path is
+        // Each pass is one firing of every active lane, bound by VALU issue on a
+        // full device (92 % busy): 209 instructions a firing on the Lotka-Volterra
+        // ensemble, 947 ms for 2^20 trajectories, where three exact gaps, selects
+        // for every update and integer products took 307 and (with the same
+        // logarithm) 1059 ms.  The common path is
         // straight-line; every rare event (start or end of a trajectory, a
         // sample point, a near-tie, a clamped gap, an overflow, the firing
         // cap) is handled in one branch entered only when some lane of the
         // wave needs it.
         bool active = true, fresh = true, capped = false;
-        while (__ballot(active) != 0ull) {
-            if (!active) continue;
-            // gaps and argmin (lowest k wins ties; d2 = second smallest gap)
-            double d1 = __builtin_inf(), d2 = __builtin_inf();
+        while (active) {
+            bool f[MT];                                    // the channel that fires
+            double d1 = 0.0;
+            bool near = false, clamped = false;
             int mu = 0;
             if constexpr (METHOD == RTSSA_METHOD_RANDOM_TIME) {
-                // A frozen channel (a_k = 0, 1/a_k = +inf) gives +inf while
-                // P_k > T_k, so the raw gaps are the gaps unless one is negative
-                // (clamped to 0) or a frozen channel has P_k <= T_k (NaN, -inf):
-                // then, rarely, the wavefront takes the exact form.
-                rt_min2 sel{__builtin_inf(), __builtin_inf(), 0};
-                bool bad = false;
+                // The argmin of the gaps (Eq. 25).  Only the smallest gap's value
+                // enters the trajectory, so the gaps are first compared in
+                // binary32, (P - T) rcp(a) with relative error below 2^-21, and
+                // the one exact reciprocal RN(1 / a_mu) is made for the winner:
+                // three IEEE divisions per firing (63 issue cycles each) were 15 %
+                // of the Lotka-Volterra kernel's issue time.
+                // The binary32 order decides when the smallest is positive and
+                // the second at least 1 + 2^-18 times it plus 1e-30 (which also
+                // excludes near-ties, clamped gaps and values whose binary32
+                // form under- or overflowed); else, and for the rare event that
+                // needs d2, the exact form below decides.
+                double df[MT];
+                float gf[MT];
 #pragma unroll
                 for (int k = 0; k < MT; ++k) {
-                    const double raw = (Pk[k] - T[k]) * inv[k];
-                    bad = bad || !(raw >= 0.0);
-                    rt_min2_push(sel, raw, k);
+                    df[k] = Pk[k] - T[k];
+                    gf[k] = (float)df[k] * __builtin_amdgcn_rcpf((float)a[k]);
                 }
-                if (__builtin_expect(__ballot(bad) != 0ull, 0)) {
-                    sel = rt_min2{__builtin_inf(), __builtin_inf(), 0};
+                float g1, g2;
+                rt_two_smallest<MT>(gf, g1, g2);
+                const bool amb = !(g1 > 0.0f) || !(g2 > fmaf(g1, 1.0f + 0x1p-18f, 1e-30f));
+                if (__builtin_expect(__ballot(amb) != 0ull, 0)) {
+                    if (amb) {
+                        // exact gaps: max(0, RN((P - T) RN(1 / a))), +inf for a
+                        // frozen channel, lowest k on ties
+                        rt_min2 sel{__builtin_inf(), __builtin_inf(), 0};
 #pragma unroll
-                    for (int k = 0; k < MT; ++k) {
-                        const double raw = (Pk[k] - T[k]) * inv[k];
-                        const double d = a[k] == 0.0 ? __builtin_inf() : fmax(raw, 0.0);
-                        rt_min2_push(sel, d, k);
+                        for (int k = 0; k < MT; ++k) {
+                            const double raw = df[k] * (1.0 / a[k]);
+                            rt_min2_push(sel, a[k] == 0.0 ? __builtin_inf() : fmax(raw, 0.0), k);
+                        }
+                        near = rt_near_tie(sel.d1, sel.d2);
+                        g1 = 1.0f;
+#pragma unroll
+                        for (int k = 0; k < MT; ++k) {
+                            gf[k] = sel.k == k ? 1.0f : 2.0f;
+                            // (a clamped gap fires at once; when every channel is
+                            // frozen the winner's reciprocal gives d1 = NaN)
+                            const bool neg = sel.k == k && a[k] != 0.0 && df[k] < 0.0;
+                            clamped = clamped || (neg && df[k] * (1.0 / a[k]) < 0.0);
+                            df[k] = neg ? 0.0 : df[k];
+                        }
                     }
                 }
-                d1 = sel.d1;
-                d2 = sel.d2;
-                mu = sel.k;
+                double am = a[MT - 1], dm = df[MT - 1];
+                mu = MT - 1;
+                f[MT - 1] = true;
+#pragma unroll
+                for (int k = MT - 2; k >= 0; --k) {
+                    f[k] = gf[k] == g1;
+                    am = f[k] ? a[k] : am;
+                    dm = f[k] ? df[k] : dm;
+                    mu = f[k] ? k : mu;
+                    f[MT - 1] = f[MT - 1] && !f[k];
+                }
+                d1 = dm * rt_recip(am);
             } else {
                 // direct method: total rate, one block for the waiting time and
                 // the search (padding channels add +0 and are never reached)
@@ -331,47 +435,45 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
 #pragma unroll
                 for (int k = 0; k < MT; ++k) {
                     run += a[k];
-                    const bool hit = !found && run >= target;
-                    mu = hit ? k : mu;
-                    found = found || hit;
+                    f[k] = !found && (run >= target || k == MT - 1);
+                    mu = f[k] ? k : mu;
+                    found = found || f[k];
                 }
             }
             const double t_new = t + d1;
-            const bool live = !fresh && !capped;          // a trajectory is in progress
-            // a rate breakpoint before the next firing (and before t_end):
-            // Eq. 28 is solved again from there
-            const bool brk = SCHED && live && b_next < t_end && t_new > b_next;
-            const bool absorbed = !brk && d1 == __builtin_inf();
-            const bool term = !brk && (absorbed || t_new > t_end);
-            // jump v_mu, checked against [0, 2^31 - 1]
-            int32_t Xn[NT];
-            bool ok = true;
+            // a jump may leave [0, 2^31 - 1] only upwards (a channel with a_k > 0
+            // has its reactants), and only from a count past x_safe
+            uint32_t x_top = (uint32_t)X[0];
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                int32_t dl = nu[0][j];
+            for (int j = 1; j < NT; ++j) x_top = max(x_top, (uint32_t)X[j]);
+            // (NaN, from an absorbed state, is past every time)
+            if (__builtin_expect((__ballot(!(t_new <= t_stop)) | __ballot(x_top > x_safe) |
+                                  __ballot(near) | __ballot(clamped)) != 0ull, 0)) {
+                const bool live = !fresh && !capped;          // a trajectory is in progress
+                const bool absorbed = !(d1 < __builtin_inf());
+                // a rate breakpoint before the next firing (and before t_end):
+                // Eq. 28 is solved again from there
+                const bool brk = SCHED && live && b_next < t_end && (absorbed || t_new > b_next);
+                const bool term = !brk && (absorbed || t_new > t_end);
+                // the jump, checked exactly: X_j in [0, 2^31 - 1] plus an int32
+                // change leaves that range exactly when the 32-bit wrap is negative
+                int32_t sign = 0;
 #pragma unroll
-                for (int k = 1; k < MT; ++k) dl = (mu == k) ? nu[k][j] : dl;
-                // X_j in [0, 2^31 - 1] and an int32 change: the exact sum is
-                // outside that range exactly when its 32-bit wrap is negative
-                const int32_t v = (int32_t)((uint32_t)X[j] + (uint32_t)dl);
-                ok = ok && v >= 0;
-                Xn[j] = v;
-            }
-            const bool event = live && !term && !brk;     // this pass may apply an event
-            const bool near_tie = METHOD == RTSSA_METHOD_RANDOM_TIME && event &&
-                                  rt_near_tie(d1, d2);
-            // a zero gap may have been clamped from a negative raw gap
-            const bool rare = !live || term || brk || near_tie ||
-                              (METHOD == RTSSA_METHOD_RANDOM_TIME && d1 == 0.0) || !ok ||
-                              s_next < t_new;
-            if (__builtin_expect(__ballot(rare) != 0ull, 0)) {
+                for (int j = 0; j < NT; ++j) {
+                    int32_t dl = nu[MT - 1][j];
+#pragma unroll
+                    for (int k = 0; k < MT - 1; ++k) dl = f[k] ? nu[k][j] : dl;
+                    sign |= (int32_t)((uint32_t)X[j] + (uint32_t)dl);
+                }
+                const bool ok = sign >= 0;
+                const bool event = live && !term && !brk;     // this pass may apply an event
                 // Counted once per event: when another lane of the wave stops or
                 // meets a breakpoint, this lane repeats its pass below without
                 // applying its event, so the counters are bumped only once the
                 // event is known to be applied (or, for a near-tie, when the
                 // event ends the trajectory by an overflow, as the oracle counts
                 // it); tie and the samples are idempotent.
-                bool clamped = false;
+                const bool near_tie = event && near;
                 if (event) {
                     if (near_tie) tie = tie == kTieNone ? fired : tie;
                     while (s_next < t_new) {
@@ -379,11 +481,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                         ++g;
                         s_next = g < it->G ? it->s[g] : __builtin_inf();
                     }
-                    if (METHOD == RTSSA_METHOD_RANDOM_TIME && ok && d1 == 0.0) {
-#pragma unroll
-                        for (int k = 0; k < MT; ++k)
-                            clamped = mu == k ? (Pk[k] - T[k]) * inv[k] < 0.0 : clamped;
-                    }
+                    t_stop = fmin(s_next, SCHED ? fmin(b_next, t_end) : t_end);
                 }
                 if (SCHED && brk) {
                     // every internal clock runs to the breakpoint at the old
@@ -393,14 +491,12 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                     for (int k = 0; k < MT; ++k) T[k] = fma(a[k], db, T[k]);
                     t = b_next;
 #pragma unroll
-                    for (int k = 0; k < MT; ++k) cl[k] = k < M ? sched_c[piece * M + k] : 0.0;
+                    for (int k = 0; k < MT; ++k)
+                        cl[k] = k < M ? kernel_rate(kind[k], sched_c[piece * M + k]) : 0.0;
                     ++piece;
                     b_next = piece < sB ? sched_t[piece] : __builtin_inf();
-#pragma unroll
-                    for (int k = 0; k < MT; ++k) {
-                        a[k] = propensity<NT>(kind[k], s0[k], s1[k], cl[k], X);
-                        inv[k] = 1.0 / a[k];
-                    }
+                    t_stop = fmin(s_next, fmin(b_next, t_end));
+                    refresh();
                 }
                 const bool stop = !live || term || (!ok && !brk);
                 if (near_tie && stop) atomicAdd(&ws->near_ties, 1ull);   // event && !ok
@@ -421,7 +517,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                     }
                     if (it->n_out) {
 #pragma unroll
-                        for (int k = 0; k < MT; ++k) if (k < M) it->n_out[r * M + k] = n[k];
+                        for (int k = 0; k < MT; ++k) if (k < M) it->n_out[r * M + k] = cnt[k * 256];
                     }
                     if (METHOD == RTSSA_METHOD_RANDOM_TIME && it->T_out) {
 #pragma unroll
@@ -461,17 +557,14 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
 #pragma unroll
                             for (int k = 0; k < MT; ++k) cl[k] = c[k];
                         }
+                        t_stop = fmin(s_next, SCHED ? fmin(b_next, t_end) : t_end);
+                        refresh();
+                        tw = rt_traj_prepare(traj, key0);
 #pragma unroll
-                        for (int k = 0; k < MT; ++k) {
-                            n[k] = 0;
-                            a[k] = propensity<NT>(kind[k], s0[k], s1[k], SCHED ? cl[k] : c[k], X);
-                        }
+                        for (int k = 0; k < MT; ++k) cnt[k * 256] = 0u;
                         if constexpr (METHOD == RTSSA_METHOD_RANDOM_TIME) {
 #pragma unroll
-                            for (int k = 0; k < MT; ++k) {
-                                T[k] = 0.0;
-                                inv[k] = 1.0 / a[k];
-                            }
+                            for (int k = 0; k < MT; ++k) T[k] = 0.0;
                             // first internal firing times, one draw at a time
 #pragma unroll 1
                             for (int k = 0; k < MT; ++k) {
@@ -489,47 +582,46 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                 if (near_tie) atomicAdd(&ws->near_ties, 1ull);
                 if (clamped) atomicAdd(&ws->clamps, 1ull);
             }
-            if constexpr (METHOD == RTSSA_METHOD_DIRECT) {
-#pragma unroll
-                for (int k = 0; k < MT; ++k) n[k] += mu == k ? 1u : 0u;
-#pragma unroll
-                for (int j = 0; j < NT; ++j) X[j] = Xn[j];
-                t = t_new;
-                ++fired;
-                if (want_hash) hash = (hash ^ (unsigned long long)(uint32_t)mu) * kFnvPrime;
-#pragma unroll
-                for (int k = 0; k < MT; ++k) a[k] = propensity<NT>(kind[k], s0[k], s1[k], SCHED ? cl[k] : c[k], X);
-                capped = fired >= C.max_firings;
-                continue;
-            }
-            // internal times advance by a_k Delta (Eq. 15); the fired channel
-            // lands exactly on its firing internal time
-            uint32_t n_mu = 0;
-            double p_mu = 0.0;
-#pragma unroll
-            for (int k = 0; k < MT; ++k) {
-                const bool f = mu == k;
-                T[k] = f ? Pk[k] : fma(a[k], d1, T[k]);
-                n[k] += f ? 1u : 0u;
-                n_mu = f ? n[k] : n_mu;
-                p_mu = f ? Pk[k] : p_mu;
-            }
-#pragma unroll
-            for (int j = 0; j < NT; ++j) X[j] = Xn[j];
             t = t_new;
             ++fired;
             if (want_hash) hash = (hash ^ (unsigned long long)(uint32_t)mu) * kFnvPrime;
-            p_mu = p_mu + rt_exp1_wave(key0, key1, traj, net_id, (uint32_t)mu, n_mu,
-                                       &ws->slow_logs, sc);
-            // a_k is a pure function of X; inv_k = RN(1 / a_k) (+inf for a dead
-            // channel, whose gap is +inf by the a_k = 0 test and never reads it)
+            // the fired channel's updates run under its lanes' mask, one
+            // instruction each (as selects over the channels the internal times
+            // and the jump took six a channel and two a species); the empty
+            // statements keep them from becoming selects again
+            if constexpr (METHOD == RTSSA_METHOD_RANDOM_TIME) {
+                // internal times advance by a_k Delta (Eq. 15); the fired channel
+                // lands exactly on its firing internal time and draws the next
+                const uint32_t n_mu = atomicAdd(&cnt[mu * 256], 1u) + 1u;
 #pragma unroll
-            for (int k = 0; k < MT; ++k) {
-                Pk[k] = (mu == k) ? p_mu : Pk[k];
-                a[k] = propensity<NT>(kind[k], s0[k], s1[k], SCHED ? cl[k] : c[k], X);
-                inv[k] = 1.0 / a[k];
+                for (int k = 0; k < MT; ++k) T[k] = fma(a[k], d1, T[k]);
+                const uint64_t m = rt_block_m53(
+                    rt_philox_traj(tw, n_mu >> 1, (uint32_t)mu, net_k1, key0, key1), n_mu);
+                const double E = rt_neglog_wave(m, false, &ws->slow_logs, sc);
+#pragma unroll
+                for (int k = 0; k < MT; ++k)
+                    if (f[k]) {
+                        asm volatile("");
+                        T[k] = Pk[k];
+                        Pk[k] = Pk[k] + E;
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) X[j] += nu[k][j];
+                    }
+            } else {
+                atomicAdd(&cnt[mu * 256], 1u);
+#pragma unroll
+                for (int k = 0; k < MT; ++k)
+                    if (f[k]) {
+                        asm volatile("");
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) X[j] += nu[k][j];
+                    }
             }
-            capped = fired >= C.max_firings;
+            refresh();
+            if (__builtin_expect(__ballot(fired >= C.max_firings) != 0ull, 0)) {
+                capped = fired >= C.max_firings;
+                t_stop = capped ? -1.0 : t_stop;
+            }
         }
     }
     share.flush(ws);

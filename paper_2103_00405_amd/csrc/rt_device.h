@@ -86,6 +86,18 @@ __device__ __forceinline__ double rt_propensity_mem(int2 rr, double c, const int
     return rt_propensity_counts(kind, (uint32_t)v0, (uint32_t)v1, c);
 }
 
+// RN(1 / a) for a normal a whose reciprocal is normal: v_rcp_f64 (2^-24.3),
+// one cubic step to within an ulp, and the residual, exact in one fma, folded
+// in with one rounding (Markstein's construction).  Seven instructions where
+// the general division takes eleven.
+__device__ __forceinline__ double rt_recip(double a)
+{
+    double y = __builtin_amdgcn_rcp(a);
+    const double e = fma(-a, y, 1.0);
+    y = fma(y, fma(e, e, e), y);
+    return fma(fma(-a, y, 1.0), y, y);
+}
+
 // The near-tie rule (Eq. 4 gives ties probability zero; in binary64 the two
 // smallest gaps d1 <= d2 can still round within reach of each other):
 // RN(d2 - d1) <= RN(1e-12 d1).
@@ -114,7 +126,7 @@ __device__ __forceinline__ int rt_find_item(rt_cptr<int64_t> unit_start, int cou
 }
 
 // Where a kernel's per-lane logarithms find the quick phase's table.  The
-// thread and sub-wave kernels keep a copy in LDS (4 KiB per workgroup): its
+// thread and sub-wave kernels keep a copy in LDS (6 KiB per workgroup): its
 // reads are counted apart from the global loads in flight, and 64 lanes'
 // entries come faster than from the vector L1.  Kernels whose LDS bounds the
 // network size read the constant table itself.
@@ -189,7 +201,8 @@ __device__ __forceinline__ double rt_neglog_wave(uint64_t m, bool force_accurate
                                                  bool* took_slow = nullptr)
 {
     double y;
-    const bool open = !rt_neglog_quick(m, lc.tab, y) || force_accurate;
+    const bool open =
+        !rt_neglog_quick((uint32_t)(m >> 32), (uint32_t)m, lc.tab, y) || force_accurate;
     if (took_slow) *took_slow = false;
     if (__builtin_expect(__ballot(open) != 0ull, 0)) {
         if (open) {
@@ -211,7 +224,8 @@ __device__ __forceinline__ double rt_neglog_uniform(uint64_t m, unsigned long lo
 {
     double y;
     const bool open = !rt_neglog_quick(
-        m, [](uint32_t i) { return rt_logq_const(__builtin_amdgcn_readfirstlane(i)); }, y);
+        (uint32_t)(m >> 32), (uint32_t)m,
+        [](uint32_t i) { return rt_logq_const(__builtin_amdgcn_readfirstlane(i)); }, y);
     if (__builtin_expect(__ballot(open) != 0ull, 0)) {
         const unsigned long long active = __ballot(true);
         const int first = __ffsll((long long)active) - 1;
@@ -221,6 +235,17 @@ __device__ __forceinline__ double rt_neglog_uniform(uint64_t m, unsigned long lo
         y = __shfl(y, first, 64);
     }
     return y;
+}
+
+// The 53 bits behind a draw of the channel's n-th firing, from its block: the
+// words' order must not be folded into the last round (the compiler would
+// select that round's operands instead of its results, twice the
+// instructions).
+__device__ __forceinline__ uint64_t rt_block_m53(rt_u4 w, uint32_t n)
+{
+    asm("" : "+v"(w.x), "+v"(w.y), "+v"(w.z), "+v"(w.w));
+    const uint32_t hi = (n & 1u) ? w.w : w.y, lo = (n & 1u) ? w.z : w.x;
+    return ((uint64_t)(hi >> 11) << 32) | __builtin_amdgcn_alignbit(hi, lo, 11);
 }
 
 template <class Tab>

@@ -69,6 +69,36 @@ RT_HD rt_u4 rt_philox4x32_10(rt_u4 c, uint32_t k0, uint32_t k1)
     return c;
 }
 
+// The draw blocks of one trajectory: counter (n >> 1, k, traj, net).  Round 1's
+// product of traj is the same for every block, so it is made once per
+// trajectory (h, l) and the key word joins net beforehand.
+struct rt_traj_words {
+    uint32_t h, l;      // high word of 0xCD9E8D57 traj, xor key 0; low word
+};
+
+RT_HD rt_traj_words rt_traj_prepare(uint32_t traj, uint32_t k0)
+{
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * traj;
+    return rt_traj_words{(uint32_t)(p1 >> 32) ^ k0, (uint32_t)p1};
+}
+
+RT_HD rt_u4 rt_philox_traj(rt_traj_words tw, uint32_t half_n, uint32_t k, uint32_t net_k1,
+                           uint32_t k0, uint32_t k1)
+{
+    const uint64_t q0 = (uint64_t)0xD2511F53u * half_n;
+    rt_u4 c = {tw.h ^ k, tw.l, (uint32_t)(q0 >> 32) ^ net_k1, (uint32_t)q0};
+#pragma unroll
+    for (int round = 1; round < 10; ++round) {
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c.x;
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c.z;
+        c = rt_u4{rt_xor3((uint32_t)(p1 >> 32), c.y, k0), (uint32_t)p1,
+                  rt_xor3((uint32_t)(p0 >> 32), c.w, k1), (uint32_t)p0};
+    }
+    return c;
+}
+
 // ------------------------------------------------ error-free transforms
 // Fast2Sum (Dekker): s + e == a + b exactly when |a| >= |b| or a == 0.
 RT_HD void rt_fast2sum(double a, double b, double& s, double& e)
@@ -283,41 +313,64 @@ RT_HD bool rt_rounding_certain(double yh, double yl)
 // lower exponent than ln(1 + z), so the Fast2Sums are exact.  Errors, relative
 // to y: z^3 p in binary64 2^-68.3 (4 roundings of z^3 / 3 at |z| = 2^-8
 // against y >= 2^-8, or of z^2 / 3 against y = |z| where h = 0), the terms past
-// z^9 2^-72, L's 31 bits 2^-70; below 2^-67 together, and the test allows
-// 2^-66.  y is RN(-ln u) when the result is true: rounding is monotone, so
+// z^9 2^-72; below 2^-67 together, and the test allows 2^-66.  y is RN(-ln u) when the result is true: rounding is monotone, so
 // when both ends of the interval round alike so does -ln u.  u = 1 gives
 // z = h = 0 and y = +0.  With it (and the 2^-74 above) the Lotka-Volterra
 // ensemble of 2^20 trajectories went from 1244 to 1059 ms, its direct method
 // (2^18) from 303 to 224 ms; the kernels whose draw is off the critical path
 // gained 0-8 %.
 struct rt_logq {
-    double h, l;
+    double h, l, r;
 };
 #define RT_LOGQ_N (1 << RT_LOGQ_BITS)
 
 // Entry i of the table itself.
-RT_HD rt_logq rt_logq_const(uint32_t i) { return rt_logq{RT_LOGQ[2 * i], RT_LOGQ[2 * i + 1]}; }
-
-// (tab(i) reads entry i from where the caller keeps the table)
-template <class Tab>
-RT_HD bool rt_neglog_quick(uint64_t m, Tab tab, double& y)
+RT_HD rt_logq rt_logq_const(uint32_t i)
 {
-    const double u1 = fma((double)(uint32_t)(m >> 32), 0x1p32, (double)(uint32_t)m) + 1.0;
+    return rt_logq{RT_LOGQ[3 * i], RT_LOGQ[3 * i + 1], RT_LOGQ[3 * i + 2]};
+}
+
+// a x + c with the constant c in a scalar register: left to itself the
+// compiler copies c to a vector register pair ahead of each in-place fma.
+RT_HD double rt_fma_const(double a, double x, double c)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(x), "s"(c));
+    return r;
+#else
+    return fma(a, x, c);
+#endif
+}
+
+// (x & a) | b in one instruction on the GPU (the compiler makes two).
+RT_HD uint32_t rt_and_or(uint32_t x, uint32_t a, uint32_t b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_bitop3_b32(x, a, b, 0xEA);
+#else
+    return (x & a) | b;
+#endif
+}
+
+// (tab(i) reads entry i from where the caller keeps the table; m = mh 2^32 + ml)
+template <class Tab>
+RT_HD bool rt_neglog_quick(uint32_t mh, uint32_t ml, Tab tab, double& y)
+{
+    const double u1 = fma((double)mh, 0x1p32, (double)ml) + 1.0;
     const uint32_t uh = (uint32_t)(rt_d2u(u1) >> 32), ul = (uint32_t)rt_d2u(u1);
     const rt_logq q = tab((uh >> (20 - RT_LOGQ_BITS)) & (RT_LOGQ_N - 1));
     const double ne = (double)(int32_t)(1023 + 53 - (uh >> 20));               // -e
-    const double f = rt_u2d(((uint64_t)((uh & 0xFFFFFu) | 0x3FF00000u) << 32) | ul);
-    const double r =
-        rt_u2d((uint64_t)(((uint32_t)rt_d2u(q.l) & RT_LOGQ_RMASK) ^ 0x3FF00000u) << 32);
-    const double z = fma(f, r, -1.0);
+    const double f = rt_u2d(((uint64_t)rt_and_or(uh, 0xFFFFFu, 0x3FF00000u) << 32) | ul);
+    const double z = fma(f, q.r, -1.0);
     const double z2h = z * z;
     const double z2l = fma(z, z, -z2h);
     double p = RT_LOGQ_C5;
-    p = fma(p, z, RT_LOGQ_C4);
-    p = fma(p, z, RT_LOGQ_C3);
-    p = fma(p, z, RT_LOGQ_C2);
-    p = fma(p, z, RT_LOGQ_C1);
-    p = fma(p, z, RT_LOGQ_C0);
+    p = rt_fma_const(p, z, RT_LOGQ_C4);
+    p = rt_fma_const(p, z, RT_LOGQ_C3);
+    p = rt_fma_const(p, z, RT_LOGQ_C2);
+    p = rt_fma_const(p, z, RT_LOGQ_C1);
+    p = rt_fma_const(p, z, RT_LOGQ_C0);
     const double t = z2h * z * p;
     const double s1h = fma(-0.5, z2h, z);                                      // z - z^2 / 2
     const double s1l = fma(-0.5, z2h, z - s1h);
@@ -339,7 +392,7 @@ RT_HD double rt_neglog_u53(uint64_t m, bool force_accurate, bool* slow, uint32_t
 {
     if (!force_accurate) {
         double y;
-        if (rt_neglog_quick(m, rt_logq_const, y)) return y;
+        if (rt_neglog_quick((uint32_t)(m >> 32), (uint32_t)m, rt_logq_const, y)) return y;
     }
     if (m == 0x1FFFFFFFFFFFFFull) return 0.0;                 // u = 1
     int e, i;

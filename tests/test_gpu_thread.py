@@ -87,6 +87,31 @@ def test_birth_death_gradient_config_bit_exact():
     _assert_same(g, ref)
 
 
+@pytest.mark.parametrize("kind", ["all ones", "next to a power of two", "random"])
+def test_reciprocal_is_correctly_rounded(kind):
+    """RN(1 / a) over the rates' whole range, 1e-280 to 4e298, against the host's
+    IEEE division: random significands, and the hard ones for the construction
+    (all bits set, where 1 / a lies just past a midpoint; a few ulps from a power
+    of two)."""
+    import ctypes as C
+    from paper_2103_00405_amd._lib import check, lib
+    rng = np.random.default_rng(21)
+    ex = np.arange(-930, 991, dtype=np.int64) + 1023
+    if kind == "random":
+        e = rng.choice(ex, size=1 << 21)
+        f = rng.integers(0, 1 << 52, size=e.size, dtype=np.int64)
+    else:
+        low = np.arange(64, dtype=np.int64)
+        f = (1 << 52) - 1 - low if kind == "all ones" else low
+        e, f = (v.ravel() for v in np.meshgrid(ex, f))
+    a = ((e << 52) | f).view(np.float64)
+    ad = torch.as_tensor(a, device="cuda")
+    out = torch.empty_like(ad)
+    check(lib().rtssa_debug_recip(C.c_void_p(ad.data_ptr()), C.c_void_p(out.data_ptr()), a.size,
+                                  C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    assert np.array_equal(_np(out).view(np.uint64), (1.0 / a).view(np.uint64))
+
+
 @pytest.mark.parametrize("R,block,grid", [(1, 64, 1), (65, 64, 1), (257, 256, 1), (1999, 64, 2),
                                           (5003, 256, 3), (3000, 128, 0)])
 def test_every_trajectory_is_taken_once(R, block, grid):
