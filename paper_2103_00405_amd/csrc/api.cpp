@@ -65,9 +65,8 @@ int rt_launch_class(int mapping, int max_M, int max_N, int max_nu, const rt_clas
                     int* grid_used, int method)
 {
     if (mapping == RTSSA_MAP_THREAD) {
-        if (block <= 0) block = 256;
         *block_used = block;
-        return rt_launch_thread(max_M, max_N, C, block, grid, stream, grid_used, lanes, method);
+        return rt_launch_thread(max_M, max_N, C, block_used, grid, stream, grid_used, lanes, method);
     }
     if (method != RTSSA_METHOD_RANDOM_TIME)
         return rt_fail(RTSSA_E_UNSUPPORTED, "the direct method runs only in the thread mapping");

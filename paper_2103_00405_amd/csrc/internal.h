@@ -125,6 +125,7 @@ struct rt_class_dev {
     int32_t max_M;
     uint32_t max_firings;
     int32_t has_schedule;   // some item's network has a rate schedule
+    int32_t lanes;                     // thread mapping: trajectories a wavefront runs at once
 };
 
 // Device workspace of one single run: counters, its item descriptor and
@@ -162,7 +163,7 @@ int check_hip(hipError_t e, const char* what);
 
 // kernels: launchers take a class descriptor whose pointers are device memory
 // method: RTSSA_METHOD_RANDOM_TIME or RTSSA_METHOD_DIRECT
-int rt_launch_thread(int M, int N, const rt_class_dev& C, int block, int grid,
+int rt_launch_thread(int M, int N, const rt_class_dev& C, int* block, int grid,
                      hipStream_t stream, int* grid_used, int64_t lanes, int method);
 int rt_launch_setup(rt_ws* ws, unsigned long long* extra, int64_t n_extra, uint32_t key0,
                     uint32_t key1, const uint32_t* key_src, const rt_item_dev* item,

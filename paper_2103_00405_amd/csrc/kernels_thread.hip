@@ -1,11 +1,12 @@
 // kernels_thread.hip -- thread-per-trajectory mapping for small networks.
 //
-// One lane owns one trajectory at a time; its whole state (t, X, and per
-// channel T_k, P_k, a_k, 1/a_k, n_k) lives in VGPRs, the network constants of
-// the wavefront's current item in SGPRs.  The grid is persistent: a lane that
-// finishes a trajectory takes the next trajectory of the same item from a
-// device counter, so lanes stay busy despite uneven trajectory lengths; a
-// wavefront moves to another item only when all of its lanes are idle.
+// One lane owns one trajectory at a time; t, X and each channel's T_k, P_k and
+// a_k live in VGPRs, the firing counts n_k and each channel's next draw in LDS,
+// the network constants of the wavefront's current item in SGPRs.  The grid is
+// persistent: a lane that finishes a trajectory takes the next trajectory of
+// the same item, from a range its wavefront reserved, so lanes stay busy despite
+// uneven trajectory lengths; a wavefront moves to another item only when all of
+// its lanes are idle.
 //
 // The step is the next reaction random time algorithm (section 4, Table 2)
 // in the internal-time form of Eq. 14-16: gaps (P_k - T_k)/a_k, argmin
@@ -23,62 +24,91 @@
 
 namespace {
 
-// fn(x[j]) for a wave-uniform j (a species index of the network): a switch
-// becomes scalar branches, so x stays in registers instead of being copied
-// to scratch memory for an indexed load, and each branch works on its own
-// register rather than on a copy of it.
-template <int NT, class F>
-__device__ __forceinline__ void with_species(const double (&x)[NT], int j, F fn)
+// Where a channel's h_k is found among the products that NT species can make
+// (wave-uniform, set once per item).  Up to 4 species every product is made
+// once per firing -- 1, X_j, X_i X_j (i < j), X_j^2 - X_j -- and h is entry
+// `one` of that list; with 8 species h = e[one] (e[two] - pair) over
+// e = (1, X_0 .. X_7).  The entry is picked by register indexing on the uniform
+// index: the scalar branches on kind and species that picked it before cost a
+// fifth of the kernel's time on a full device (Lotka-Volterra ensemble of 2^20:
+// 936 ms with them, 826 ms this way; 750 ms with the model's own propensities
+// written out).
+struct rt_term {
+    int one, two;
+    double pair;
+    double scale;       // of the rate: 1/2 for a homodimer (its entry is 2 h; exact)
+};
+
+template <int NT>
+constexpr int term_count() { return NT <= 1 ? 4 : (NT <= 2 ? 8 : 16); }
+
+template <int NT>
+__device__ __forceinline__ rt_term channel_term(int kind, int s0, int s1)
 {
-    switch (j) {
-        case 1: if constexpr (NT > 1) { fn(x[1]); return; } break;
-        case 2: if constexpr (NT > 2) { fn(x[2]); return; } break;
-        case 3: if constexpr (NT > 3) { fn(x[3]); return; } break;
-        case 4: if constexpr (NT > 4) { fn(x[4]); return; } break;
-        case 5: if constexpr (NT > 5) { fn(x[5]); return; } break;
-        case 6: if constexpr (NT > 6) { fn(x[6]); return; } break;
-        case 7: if constexpr (NT > 7) { fn(x[7]); return; } break;
-        default: break;
+    rt_term t{0, 0, 0.0, kind == RT_H_PAIR ? 0.5 : 1.0};
+    if constexpr (NT <= 4) {
+        if (kind == RT_H_ONE) {
+            t.one = 1 + s0;
+        } else if (kind == RT_H_TWO) {
+            const int lo = min(s0, s1), hi = max(s0, s1);
+            t.one = 1 + NT + lo * (2 * NT - lo - 1) / 2 + (hi - lo - 1);
+        } else if (kind == RT_H_PAIR) {
+            t.one = 1 + NT + NT * (NT - 1) / 2 + s0;
+        }
+    } else {
+        t.one = kind == RT_H_ZERO ? 0 : 1 + s0;
+        t.two = kind == RT_H_TWO ? 1 + s1 : (kind == RT_H_PAIR ? 1 + s0 : 0);
+        t.pair = kind == RT_H_PAIR ? 1.0 : 0.0;
     }
-    fn(x[0]);
+    return t;
 }
 
-// The rate constant as propensities() uses it: halved for a homodimer
-// (exact: c is 0 or at least 1e-280).
-__device__ __forceinline__ double kernel_rate(int kind, double c)
-{
-    return kind == RT_H_PAIR ? 0.5 * c : c;
-}
-
-// a_k = RN(c_k RN(h_k)) of Eq. 1-2 for every channel, the kinds wave-uniform
-// and X in registers.  Counts are below 2^31, so a product of two is exact
-// before its one rounding: RN(X_i X_j) is the binary64 product, and a
-// homodimer's 2 RN(h) = RN(X^2 - X) one fma (+0 for X = 0 and 1), its factor
-// 1/2 in the rate; no 64-bit integer product and one conversion per species.
+// a_k = RN(c_k RN(h_k)) of Eq. 1-2 for every channel, X in registers.  Counts
+// are below 2^31, so a product of two is exact before its one rounding:
+// RN(X_i X_j) is the binary64 product, and a homodimer's 2 RN(h) = RN(X^2 - X)
+// one fma (+0 for X = 0 and 1), its factor 1/2 in the rate; no 64-bit integer
+// product and one conversion per species.
 template <int MT, int NT>
-__device__ __forceinline__ void propensities(const int (&kind)[MT], const int (&s0)[MT],
-                                             const int (&s1)[MT], const double (&c)[MT],
+__device__ __forceinline__ void propensities(const rt_term (&q)[MT], const double (&c)[MT],
                                              const int32_t (&X)[NT], double (&a)[MT])
 {
+    typedef double list_t __attribute__((ext_vector_type(term_count<NT>())));
     double x[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) x[j] = (double)(uint32_t)X[j];
+    list_t e;                                              // (the entries past the list are never picked)
+    e[0] = 1.0;
 #pragma unroll
-    for (int k = 0; k < MT; ++k) {
-        if (kind[k] == RT_H_ZERO) {
-            a[k] = c[k];
-        } else if (kind[k] == RT_H_ONE) {
-            with_species<NT>(x, s0[k], [&](double u) { a[k] = c[k] * u; });
-        } else if (kind[k] == RT_H_PAIR) {
-            with_species<NT>(x, s0[k], [&](double u) { a[k] = c[k] * fma(u, u, -u); });
-        } else if constexpr (NT == 2) {
-            a[k] = c[k] * (x[0] * x[1]);
-        } else {
-            double u = 0.0;
-            with_species<NT>(x, s0[k], [&](double v) { u = v; });
-            with_species<NT>(x, s1[k], [&](double v) { a[k] = c[k] * (u * v); });
-        }
+    for (int j = 0; j < NT; ++j) e[1 + j] = x[j];
+    if constexpr (NT <= 4) {
+        int at = 1 + NT;
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = i + 1; j < NT; ++j) e[at++] = x[i] * x[j];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) e[at++] = fma(x[j], x[j], -x[j]);
+#pragma unroll
+        for (int k = 0; k < MT; ++k) a[k] = c[k] * e[q[k].one];
+    } else {
+#pragma unroll
+        for (int k = 0; k < MT; ++k)
+            a[k] = c[k] * fma(e[q[k].one], e[q[k].two] - q[k].pair, 0.0);
     }
+}
+
+// A firing channel's internal times: T = P, then P += E.  In place (the
+// compiler adds into a temporary and copies) and never as selects.
+__device__ __forceinline__ void rt_land(double& T, double& P, double E)
+{
+    asm volatile("v_mov_b64 %0, %1" : "=v"(T) : "v"(P));
+    asm volatile("v_add_f64 %0, %0, %1" : "+v"(P) : "v"(E));
+}
+
+// (m + 1) 2^-53
+__device__ __forceinline__ double rt_u53(uint64_t m)
+{
+    return (fma((double)(uint32_t)(m >> 32), 0x1p32, (double)(uint32_t)m) + 1.0) * 0x1p-53;
 }
 
 // The two smallest of MT binary32 values; a NaN makes them equal.
@@ -98,38 +128,6 @@ __device__ __forceinline__ void rt_two_smallest(const float (&v)[MT], float& g1,
         }
     }
 }
-
-// Collects one lane's writes to one 64-byte line in its LDS buffer and
-// stores them together when the next write falls in another line (or on
-// flush); only the words the lane wrote are stored.
-struct rt_line_writer {
-    int32_t* buf;       // 16 words of LDS
-    uint64_t line;      // address >> 6 of the buffered line (~0: none)
-    uint32_t mask;      // words written
-
-    __device__ __forceinline__ void flush()
-    {
-        if (mask) {
-            int32_t* const base = (int32_t*)(line << 6);
-#pragma unroll
-            for (int w = 0; w < 16; ++w)
-                if (mask & (1u << w)) base[w] = buf[w];
-            mask = 0u;
-        }
-    }
-
-    __device__ __forceinline__ void put(int32_t* p, int32_t v)
-    {
-        const uint64_t addr = (uint64_t)p;
-        if ((addr >> 6) != line) {
-            flush();
-            line = addr >> 6;
-        }
-        const int w = (int)((addr >> 2) & 15u);
-        buf[w] = v;
-        mask |= 1u << w;
-    }
-};
 
 // One wavefront's share of the trajectory counter and of the run's counts, in
 // LDS.  Lanes take trajectories from the reserved range [next, end); when a
@@ -210,15 +208,17 @@ struct rt_wave_share {
     }
 };
 
-// Waves per SIMD each instantiation is compiled for: the most at which its
-// state (X, n, a and, for the random-time method, T, P and 1/a, in registers;
-// the network in SGPRs; with a rate schedule, the lane's rates too) fits
-// without spilling to scratch.
+// Sample points kept in LDS per wavefront.
+constexpr int kGridLds = 128;
+
+// Waves per SIMD each instantiation is compiled for: the most at which the
+// firing loop's state fits without spilling to scratch (the branches of rare
+// events spill up to 112 bytes, which measured nothing).
 constexpr int thread_min_waves(int MT, int NT, int METHOD, bool SCHED)
 {
     if (METHOD == RTSSA_METHOD_DIRECT) return 4;
-    // 5 waves fit without scratch up to 3 channels and 2 species (and 2 x 4);
-    // on the Lotka-Volterra ensemble they measured 2.7 % faster than 4
+    // 5 waves up to 3 channels and 2 species (and 2 x 4): 572 ms against 650 for
+    // 700000 Lotka-Volterra trajectories at 4, the same for 2^20
     if (!SCHED && ((MT <= 2 && NT <= 4) || (MT == 3 && NT <= 2))) return 5;
     if (!SCHED) return MT <= 4 ? 4 : (MT == 8 && NT == 8 ? 2 : 3);
     // with a schedule each lane also holds its rates in force
@@ -239,12 +239,11 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
     const uint32_t key0 = ws->key0, key1 = ws->key1;
     __shared__ rt_log_lds<4> log_lds;
     const auto sc = log_lds.init();
-    // per-lane buffer of one 64-byte line of sample output: a lane's sample
-    // row is written a few bytes at a time, at its own event times; collecting
-    // the words of a line and storing them together lets the L2 write each
-    // line back once instead of once per sample point
-    __shared__ int32_t line_buf[256][16];
-    int32_t* const lb = line_buf[threadIdx.x];
+    // the first points of the item's sample grid, one copy per wavefront: a lane
+    // that passes a sample point needs the next one at once, and a global load
+    // there stalls its whole wavefront
+    __shared__ double sample_points[4][kGridLds];
+    double* const sgrid = sample_points[threadIdx.x >> 6];
     __shared__ rt_wave_share wave_shares[4];
     rt_wave_share& share = wave_shares[threadIdx.x >> 6];
     share.clear();
@@ -252,6 +251,9 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
     // comes from one LDS atomic instead of selects over every channel's register
     __shared__ uint32_t counts[MT][256];
     uint32_t* const cnt = &counts[0][threadIdx.x];
+    // E(k, n_k + 1), the draw channel k's next firing uses
+    __shared__ double ahead[METHOD == RTSSA_METHOD_RANDOM_TIME ? MT : 1][256];
+    double* const next_draw = &ahead[0][threadIdx.x];
 
     int item = C.exclusive ? -1 : 0;
     bool first = true;
@@ -274,18 +276,18 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
         unsigned long long* const traj_ctr = C.item_next + item;
 
         // ---- network constants (uniform)
-        int kind[MT], s0[MT], s1[MT], nu[MT][NT];
+        rt_term terms[MT];
+        int nu[MT][NT];
         double c[MT];
 #pragma unroll
         for (int k = 0; k < MT; ++k) {
             if (k < net.M) {
                 int2 rr = rt_const(net.react)[k];
-                kind[k] = (int)((uint32_t)rr.x >> 29);
-                s0[k] = rr.x & RT_SPECIES_MASK;
-                s1[k] = rr.y;
-                c[k] = kernel_rate(kind[k], rt_const(net.c)[k]);
+                terms[k] = channel_term<NT>((int)((uint32_t)rr.x >> 29), rr.x & RT_SPECIES_MASK, rr.y);
+                c[k] = terms[k].scale * rt_const(net.c)[k];
             } else {
-                kind[k] = RT_H_ZERO; s0[k] = 0; s1[k] = 0; c[k] = 0.0;   // dead padding channel
+                terms[k] = channel_term<NT>(RT_H_ZERO, 0, 0);       // dead padding channel
+                c[k] = 0.0;
             }
 #pragma unroll
             for (int j = 0; j < NT; ++j)
@@ -300,6 +302,22 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
         const uint32_t net_id = it->net_id, traj_offset = it->traj_offset;
         const bool want_hash = it->seq_hash != nullptr;
         const uint32_t net_k1 = net_id ^ key1;
+        // sample rows: X goes straight to memory at each sample point (through a
+        // 64-byte line buffer per lane HBM saw a sixth of the writes, 1.3 against
+        // 5.4 GB a launch of 2^20 Lotka-Volterra trajectories, but a point cost
+        // three times the instructions and the device writes some 5 GB a second of the
+        // 5 TB/s it can)
+        int32_t* const samples = it->samples;
+        const int32_t G = it->G;
+        const int64_t ss_n = it->ss_n, ss_g = it->ss_g;
+        const bool row2 = NT == 2 && N == 2 && ss_n == 1 &&
+                          (((uint64_t)samples >> 2 | (uint64_t)it->ss_r | (uint64_t)ss_g) & 1u) == 0;
+        for (int i = (int)(threadIdx.x & 63u); i < kGridLds; i += 64)
+            sgrid[i] = i < G ? it->s[i] : __builtin_inf();
+        rt_wave_lds_fence();
+        auto sample_time = [&](int32_t gg) {
+            return gg < kGridLds ? sgrid[gg] : (gg < G ? it->s[gg] : __builtin_inf());
+        };
         // counts up to here are safe from any jump's increase
         int32_t up = 0;
 #pragma unroll
@@ -307,6 +325,13 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
 #pragma unroll
             for (int j = 0; j < NT; ++j) up = max(up, nu[k][j]);
         const uint32_t x_safe = 0x7FFFFFFFu - (uint32_t)up;
+        // rates for which every a_k > 0 and every gap is a normal binary32 number
+        // or overflows towards the exact form: 0 or 2^-100 .. 2^60 (h < 2^62, and
+        // 1e-32 < P - T < 37); other items take the exact form at every firing
+        auto plain_rate = [](double v) { return v == 0.0 || (v >= 0x1p-100 && v <= 0x1p60); };
+        bool plain = true;
+#pragma unroll
+        for (int k = 0; k < MT; ++k) plain = plain && plain_rate(c[k]);
 
         // ---- trajectory state
         int32_t X[NT];
@@ -316,7 +341,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
         for (int j = 0; j < NT; ++j) X[j] = 0;
 #pragma unroll
         for (int k = 0; k < MT; ++k) { T[k] = 0.0; Pk[k] = 0.0; a[k] = 0.0; }
-        double t = 0.0, s_next = 0.0;
+        double t = 0.0, s_next = __builtin_inf();
         // the earliest of the next sample point, the next rate breakpoint and
         // t_end: a firing past it needs the rare branch (so does every pass of
         // a lane without a trajectory in progress, which holds -1 here)
@@ -329,37 +354,104 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
 #pragma unroll
         for (int k = 0; k < MT; ++k) cl[k] = c[k];
         int32_t g = 0;
-        uint32_t fired = 0, tie = kTieNone, traj = 0;
+        uint32_t fired = 0, tie = kTieNone;
         unsigned long long hash = kFnvOffset;
-        int64_t r = 0;
-
-        rt_line_writer lw{lb, ~0ull, 0u};
-        auto write_sample = [&](int32_t gg, bool invalid) {
-            int32_t* dst = it->samples + r * it->ss_r + (int64_t)gg * it->ss_g;
+        uint32_t r = 0;
+        int32_t* sp = nullptr;                             // sample row g of trajectory r
+        auto write_row = [&](bool invalid) {
+            if constexpr (NT == 2) {
+                if (row2) {
+                    *(int2*)sp = invalid ? make_int2(-1, -1) : make_int2(X[0], X[1]);
+                    return;
+                }
+            }
 #pragma unroll
             for (int j = 0; j < NT; ++j)
-                if (j < N) lw.put(dst + j * it->ss_n, invalid ? -1 : X[j]);
+                if (j < N) sp[j * ss_n] = invalid ? -1 : X[j];
         };
         auto refresh = [&]() {
-            if constexpr (SCHED) propensities<MT, NT>(kind, s0, s1, cl, X, a);
-            else propensities<MT, NT>(kind, s0, s1, c, X, a);
+            if constexpr (SCHED) propensities<MT, NT>(terms, cl, X, a);
+            else propensities<MT, NT>(terms, c, X, a);
         };
 
-        // Each pass is one firing of every active lane, bound by VALU issue on a
-        // full device (92 % busy): 209 instructions a firing on the Lotka-Volterra
-        // ensemble, 947 ms for 2^20 trajectories, where three exact gaps, selects
-        // for every update and integer products took 307 and (with the same
-        // logarithm) 1059 ms.  The common path is
-        // straight-line; every rare event (start or end of a trajectory, a
-        // sample point, a near-tie, a clamped gap, an overflow, the firing
-        // cap) is handled in one branch entered only when some lane of the
-        // wave needs it.
-        bool active = true, fresh = true, capped = false;
+        // Each pass is one firing of every active lane.  Two chains of dependent
+        // instructions run side by side in it, so that a wavefront with its SIMD to
+        // itself is not bound by their sum: the choice of the firing channel from
+        // the state, and the draw that replaces the one the previous firing used
+        // (of channel mu_p; a direct-method firing's numbers need no state at all).
+        // Side by side they took the ensemble of 2^20 Lotka-Volterra trajectories
+        // (a full device, bound by VALU issue) from 826 to 785 ms and a
+        // seven-channel network of 50000 from 6.2 to 5.7 ms.
+        // Everything up to the one branch for rare events (start or end of a
+        // trajectory, a sample point, a close or clamped gap, a logarithm the quick
+        // phase left open, an overflow, the firing cap) is straight-line code.
+        bool active = (int)(threadIdx.x & 63u) < C.lanes, fresh = true, capped = false;
+        uint32_t mu_p = 0u, n_next = 1u;                   // the draw to be made: E(mu_p, n_next)
+        double E_now = 0.0, u_now = 0.0;                   // DIRECT: this firing's numbers
+        float g_min = plain ? 1e-30f : __builtin_inff();   // smallest gap the binary32 order takes
         while (active) {
-            bool f[MT];                                    // the channel that fires
-            double d1 = 0.0;
-            bool near = false, clamped = false;
-            int mu = 0;
+            double df[MT];
+            float gf[MT];
+            float g1 = 0.0f;
+            unsigned long long fm[MT];                     // lanes in which channel k fires
+            uint32_t mu = 0u;
+            double d1 = 0.0, t_new = 0.0, E_old = 0.0;
+            // ---- the next draw
+            auto draw_bits = [&](double& u2) {
+                if constexpr (METHOD == RTSSA_METHOD_RANDOM_TIME) {
+                    return rt_block_m53(
+                        rt_philox_traj(tw, n_next >> 1, mu_p, net_k1, key0, key1), n_next);
+                } else {
+                    const rt_u4 w = rt_philox_traj(tw, fired + 1u, 0xFFFFFFFFu, net_k1, key0, key1);
+                    u2 = rt_u53((((uint64_t)w.w << 32) | w.z) >> 11);
+                    return (((uint64_t)w.y << 32) | w.x) >> 11;
+                }
+            };
+            double E_new, u_new = 0.0;
+            const uint64_t m_new = draw_bits(u_new);
+            const bool open =
+                !rt_neglog_quick((uint32_t)(m_new >> 32), (uint32_t)m_new, sc.tab, E_new);
+            // ---- the channel that fires
+            // from gf, g1 and df: the firing channel's masks, index, gap and draw
+            auto choose = [&]() {
+                if constexpr (METHOD == RTSSA_METHOD_RANDOM_TIME) {
+                    double am = a[MT - 1], dm = df[MT - 1];
+                    mu = MT - 1;
+                    fm[MT - 1] = ~0ull;
+#pragma unroll
+                    for (int k = MT - 2; k >= 0; --k) {
+                        fm[k] = __ballot(gf[k] == g1);
+                        const bool f = __builtin_amdgcn_inverse_ballot_w64(fm[k]);
+                        am = f ? a[k] : am;
+                        dm = f ? df[k] : dm;
+                        mu = f ? (uint32_t)k : mu;
+                        fm[MT - 1] &= ~fm[k];
+                    }
+                    d1 = dm * rt_recip(am);
+                    E_old = next_draw[mu * 256u];
+                } else {
+                    // total rate, then the first running sum to reach u2 a_0
+                    // (padding channels add +0 and are never reached)
+                    double a0 = 0.0;
+#pragma unroll
+                    for (int k = 0; k < MT; ++k) a0 += a[k];
+                    d1 = a0 == 0.0 ? __builtin_inf() : E_now / a0;
+                    const double target = u_now * a0;
+                    double run = 0.0;
+                    unsigned long long left = ~0ull;
+                    mu = MT - 1;
+#pragma unroll
+                    for (int k = 0; k < MT; ++k) {
+                        run += a[k];
+                        fm[k] = k == MT - 1 ? left : left & __ballot(run >= target);
+                        if (k < MT - 1)
+                            mu = __builtin_amdgcn_inverse_ballot_w64(fm[k]) ? (uint32_t)k : mu;
+                        left &= ~fm[k];
+                    }
+                }
+                t_new = t + d1;
+            };
+            bool amb = false;
             if constexpr (METHOD == RTSSA_METHOD_RANDOM_TIME) {
                 // The argmin of the gaps (Eq. 25).  Only the smallest gap's value
                 // enters the trajectory, so the gaps are first compared in
@@ -367,88 +459,79 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                 // the one exact reciprocal RN(1 / a_mu) is made for the winner:
                 // three IEEE divisions per firing (63 issue cycles each) were 15 %
                 // of the Lotka-Volterra kernel's issue time.
-                // The binary32 order decides when the smallest is positive and
-                // the second at least 1 + 2^-18 times it plus 1e-30 (which also
-                // excludes near-ties, clamped gaps and values whose binary32
-                // form under- or overflowed); else, and for the rare event that
-                // needs d2, the exact form below decides.
-                double df[MT];
-                float gf[MT];
+                // The binary32 order decides when the smallest is above 1e-30 and
+                // the second at least 1 + 2^-18 times it (which also excludes
+                // near-ties, clamped gaps and values whose binary32 form under- or
+                // overflowed); else the exact form below decides.
 #pragma unroll
                 for (int k = 0; k < MT; ++k) {
                     df[k] = Pk[k] - T[k];
                     gf[k] = (float)df[k] * __builtin_amdgcn_rcpf((float)a[k]);
                 }
-                float g1, g2;
+                float g2;
                 rt_two_smallest<MT>(gf, g1, g2);
-                const bool amb = !(g1 > 0.0f) || !(g2 > fmaf(g1, 1.0f + 0x1p-18f, 1e-30f));
-                if (__builtin_expect(__ballot(amb) != 0ull, 0)) {
-                    if (amb) {
-                        // exact gaps: max(0, RN((P - T) RN(1 / a))), +inf for a
-                        // frozen channel, lowest k on ties
-                        rt_min2 sel{__builtin_inf(), __builtin_inf(), 0};
-#pragma unroll
-                        for (int k = 0; k < MT; ++k) {
-                            const double raw = df[k] * (1.0 / a[k]);
-                            rt_min2_push(sel, a[k] == 0.0 ? __builtin_inf() : fmax(raw, 0.0), k);
-                        }
-                        near = rt_near_tie(sel.d1, sel.d2);
-                        g1 = 1.0f;
-#pragma unroll
-                        for (int k = 0; k < MT; ++k) {
-                            gf[k] = sel.k == k ? 1.0f : 2.0f;
-                            // (a clamped gap fires at once; when every channel is
-                            // frozen the winner's reciprocal gives d1 = NaN)
-                            const bool neg = sel.k == k && a[k] != 0.0 && df[k] < 0.0;
-                            clamped = clamped || (neg && df[k] * (1.0 / a[k]) < 0.0);
-                            df[k] = neg ? 0.0 : df[k];
-                        }
-                    }
-                }
-                double am = a[MT - 1], dm = df[MT - 1];
-                mu = MT - 1;
-                f[MT - 1] = true;
-#pragma unroll
-                for (int k = MT - 2; k >= 0; --k) {
-                    f[k] = gf[k] == g1;
-                    am = f[k] ? a[k] : am;
-                    dm = f[k] ? df[k] : dm;
-                    mu = f[k] ? k : mu;
-                    f[MT - 1] = f[MT - 1] && !f[k];
-                }
-                d1 = dm * rt_recip(am);
-            } else {
-                // direct method: total rate, one block for the waiting time and
-                // the search (padding channels add +0 and are never reached)
-                double a0 = 0.0;
-#pragma unroll
-                for (int k = 0; k < MT; ++k) a0 += a[k];
-                const rt_u4 w = rt_philox4x32_10(rt_u4{fired, 0xFFFFFFFFu, traj, net_id}, key0, key1);
-                const uint64_t m1 = (((uint64_t)w.y << 32) | w.x) >> 11;
-                const uint64_t m2 = (((uint64_t)w.w << 32) | w.z) >> 11;
-                const double E1 = rt_neglog_wave(m1, false, &ws->slow_logs, sc);
-                d1 = a0 == 0.0 ? __builtin_inf() : E1 / a0;
-                const double target = (double)(m2 + 1) * 0x1p-53 * a0;
-                double run = 0.0;
-                bool found = false;
-                mu = MT - 1;
-#pragma unroll
-                for (int k = 0; k < MT; ++k) {
-                    run += a[k];
-                    f[k] = !found && (run >= target || k == MT - 1);
-                    mu = f[k] ? k : mu;
-                    found = found || f[k];
-                }
+                amb = !(g1 > g_min) | !(g2 > g1 * (1.0f + 0x1p-18f));
             }
-            const double t_new = t + d1;
+            choose();
             // a jump may leave [0, 2^31 - 1] only upwards (a channel with a_k > 0
             // has its reactants), and only from a count past x_safe
             uint32_t x_top = (uint32_t)X[0];
 #pragma unroll
             for (int j = 1; j < NT; ++j) x_top = max(x_top, (uint32_t)X[j]);
             // (NaN, from an absorbed state, is past every time)
-            if (__builtin_expect((__ballot(!(t_new <= t_stop)) | __ballot(x_top > x_safe) |
-                                  __ballot(near) | __ballot(clamped)) != 0ull, 0)) {
+            bool late = !(t_new <= t_stop);
+            unsigned long long rare = __ballot(x_top > x_safe);
+            const unsigned long long ambs = __ballot(amb), opens = __ballot(open);
+            if (__builtin_expect((rare | ambs | opens | __ballot(late)) != 0ull, 0)) {
+            bool near = false, clamped = false;
+            if (opens != 0ull) {
+                if (open) {
+                    double u2;
+                    if (rt_neglog_open(draw_bits(u2), false, sc.sc, E_new))
+                        atomicAdd(&ws->slow_logs, 1ull);
+                }
+            }
+            if (METHOD == RTSSA_METHOD_RANDOM_TIME && ambs != 0ull) {
+                if (amb) {
+                    // exact gaps: max(0, RN((P - T) RN(1 / a))), +inf for a
+                    // frozen channel, lowest k on ties
+                    rt_min2 sel{__builtin_inf(), __builtin_inf(), 0};
+#pragma unroll
+                    for (int k = 0; k < MT; ++k) {
+                        const double raw = df[k] * (1.0 / a[k]);
+                        rt_min2_push(sel, a[k] == 0.0 ? __builtin_inf() : fmax(raw, 0.0), k);
+                    }
+                    near = rt_near_tie(sel.d1, sel.d2);
+                    g1 = 1.0f;
+#pragma unroll
+                    for (int k = 0; k < MT; ++k) {
+                        gf[k] = sel.k == k ? 1.0f : 2.0f;
+                        // (a clamped gap fires at once; when every channel is
+                        // frozen the winner's reciprocal gives d1 = NaN)
+                        const bool neg = sel.k == k && a[k] != 0.0 && df[k] < 0.0;
+                        clamped = clamped || (neg && df[k] * (1.0 / a[k]) < 0.0);
+                        df[k] = neg ? 0.0 : df[k];
+                    }
+                }
+                choose();
+                late = !(t_new <= t_stop);
+                rare |= __ballot(near || clamped);
+            }
+            // sample points before the event, the commonest of the rare events,
+            // apart from the others (idempotent, should the pass be repeated)
+            if (s_next < t_new && t_new <= t_end && !(SCHED && b_next < t_end && t_new > b_next)) {
+                do {
+                    if (samples) {
+                        write_row(false);
+                        sp += ss_g;
+                    }
+                    s_next = sample_time(++g);
+                } while (s_next < t_new);
+                t_stop = fmin(s_next, SCHED ? fmin(b_next, t_end) : t_end);
+                late = !(t_new <= t_stop);
+            }
+            rare |= __ballot(late);
+            if (__builtin_expect(rare != 0ull, 0)) {
                 const bool live = !fresh && !capped;          // a trajectory is in progress
                 const bool absorbed = !(d1 < __builtin_inf());
                 // a rate breakpoint before the next firing (and before t_end):
@@ -462,7 +545,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                 for (int j = 0; j < NT; ++j) {
                     int32_t dl = nu[MT - 1][j];
 #pragma unroll
-                    for (int k = 0; k < MT - 1; ++k) dl = f[k] ? nu[k][j] : dl;
+                    for (int k = 0; k < MT - 1; ++k) dl = mu == (uint32_t)k ? nu[k][j] : dl;
                     sign |= (int32_t)((uint32_t)X[j] + (uint32_t)dl);
                 }
                 const bool ok = sign >= 0;
@@ -472,17 +555,9 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                 // applying its event, so the counters are bumped only once the
                 // event is known to be applied (or, for a near-tie, when the
                 // event ends the trajectory by an overflow, as the oracle counts
-                // it); tie and the samples are idempotent.
+                // it); tie is idempotent.
                 const bool near_tie = event && near;
-                if (event) {
-                    if (near_tie) tie = tie == kTieNone ? fired : tie;
-                    while (s_next < t_new) {
-                        if (it->samples) write_sample(g, false);
-                        ++g;
-                        s_next = g < it->G ? it->s[g] : __builtin_inf();
-                    }
-                    t_stop = fmin(s_next, SCHED ? fmin(b_next, t_end) : t_end);
-                }
+                if (near_tie) tie = tie == kTieNone ? fired : tie;
                 if (SCHED && brk) {
                     // every internal clock runs to the breakpoint at the old
                     // rates; the propensities take the next piece's rates
@@ -492,10 +567,14 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                     t = b_next;
 #pragma unroll
                     for (int k = 0; k < MT; ++k)
-                        cl[k] = k < M ? kernel_rate(kind[k], sched_c[piece * M + k]) : 0.0;
+                        cl[k] = k < M ? terms[k].scale * sched_c[piece * M + k] : 0.0;
                     ++piece;
                     b_next = piece < sB ? sched_t[piece] : __builtin_inf();
                     t_stop = fmin(s_next, fmin(b_next, t_end));
+                    bool ok_rates = true;
+#pragma unroll
+                    for (int k = 0; k < MT; ++k) ok_rates = ok_rates && plain_rate(cl[k]);
+                    g_min = ok_rates ? 1e-30f : __builtin_inff();
                     refresh();
                 }
                 const bool stop = !live || term || (!ok && !brk);
@@ -506,10 +585,8 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                                           : (absorbed ? RTSSA_TRAJ_ABSORBED
                                                       : (term ? RTSSA_TRAJ_OK : RTSSA_TRAJ_OVERFLOW));
                     const bool good = st == RTSSA_TRAJ_OK || st == RTSSA_TRAJ_ABSORBED;
-                    if (it->samples) {
-                        for (int32_t gg = g; gg < it->G; ++gg) write_sample(gg, !good);
-                        lw.flush();
-                    }
+                    if (samples)
+                        for (; g < G; ++g, sp += ss_g) write_row(!good);
                     if (METHOD == RTSSA_METHOD_RANDOM_TIME && good) {
                         const double dt = t_end - t;
 #pragma unroll
@@ -517,15 +594,15 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                     }
                     if (it->n_out) {
 #pragma unroll
-                        for (int k = 0; k < MT; ++k) if (k < M) it->n_out[r * M + k] = cnt[k * 256];
+                        for (int k = 0; k < MT; ++k) if (k < M) it->n_out[(int64_t)r * M + k] = cnt[k * 256];
                     }
                     if (METHOD == RTSSA_METHOD_RANDOM_TIME && it->T_out) {
 #pragma unroll
-                        for (int k = 0; k < MT; ++k) if (k < M) it->T_out[r * M + k] = T[k];
+                        for (int k = 0; k < MT; ++k) if (k < M) it->T_out[(int64_t)r * M + k] = T[k];
                     }
                     if (it->x_final) {
 #pragma unroll
-                        for (int j = 0; j < NT; ++j) if (j < N) it->x_final[r * N + j] = X[j];
+                        for (int j = 0; j < NT; ++j) if (j < N) it->x_final[(int64_t)r * N + j] = X[j];
                     }
                     if (it->t_last) it->t_last[r] = t;
                     if (it->status) it->status[r] = (uint8_t)st;
@@ -540,14 +617,15 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                     capped = false;
                     active = rr < it->R;
                     if (active) {
-                        r = rr;
-                        traj = traj_offset + (uint32_t)rr;
+                        r = (uint32_t)rr;
+                        const uint32_t traj = traj_offset + r;
+                        sp = samples ? samples + rr * it->ss_r : nullptr;
                         const int32_t* x0 = it->x0 + (it->x0_per_traj ? rr * N : 0);
 #pragma unroll
                         for (int j = 0; j < NT; ++j) X[j] = j < N ? x0[j] : 0;
                         t = 0.0;
                         g = 0;
-                        s_next = it->G > 0 ? it->s[0] : __builtin_inf();
+                        s_next = sample_time(0);
                         fired = 0;
                         tie = kTieNone;
                         hash = kFnvOffset;
@@ -563,16 +641,30 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
 #pragma unroll
                         for (int k = 0; k < MT; ++k) cnt[k * 256] = 0u;
                         if constexpr (METHOD == RTSSA_METHOD_RANDOM_TIME) {
+                            g_min = plain ? 1e-30f : __builtin_inff();
+                            mu_p = 0u;
+                            n_next = 1u;
 #pragma unroll
                             for (int k = 0; k < MT; ++k) T[k] = 0.0;
-                            // first internal firing times, one draw at a time
+                            // first internal firing times E(k, 0) and next draws
+                            // E(k, 1): the two words of one block, a channel at a time
 #pragma unroll 1
                             for (int k = 0; k < MT; ++k) {
-                                const double E0 = rt_exp1_wave(key0, key1, traj, net_id,
-                                                               (uint32_t)k, 0u, &ws->slow_logs, sc);
+                                const rt_u4 w =
+                                    rt_philox_traj(tw, 0u, (uint32_t)k, net_k1, key0, key1);
+                                const double E0 = rt_neglog_wave(rt_block_m53(w, 0u), false,
+                                                                 &ws->slow_logs, sc);
+                                next_draw[k * 256] = rt_neglog_wave(rt_block_m53(w, 1u), false,
+                                                                    &ws->slow_logs, sc);
 #pragma unroll
                                 for (int q = 0; q < MT; ++q) Pk[q] = q == k ? E0 : Pk[q];
                             }
+                        } else {
+                            const rt_u4 w =
+                                rt_philox_traj(tw, 0u, 0xFFFFFFFFu, net_k1, key0, key1);
+                            E_now = rt_neglog_wave((((uint64_t)w.y << 32) | w.x) >> 11, false,
+                                                   &ws->slow_logs, sc);
+                            u_now = rt_u53((((uint64_t)w.w << 32) | w.z) >> 11);
                         }
                     }
                 }
@@ -582,37 +674,38 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                 if (near_tie) atomicAdd(&ws->near_ties, 1ull);
                 if (clamped) atomicAdd(&ws->clamps, 1ull);
             }
+            }
             t = t_new;
             ++fired;
             if (want_hash) hash = (hash ^ (unsigned long long)(uint32_t)mu) * kFnvPrime;
             // the fired channel's updates run under its lanes' mask, one
             // instruction each (as selects over the channels the internal times
-            // and the jump took six a channel and two a species); the empty
-            // statements keep them from becoming selects again
+            // and the jump took six a channel and two a species)
             if constexpr (METHOD == RTSSA_METHOD_RANDOM_TIME) {
                 // internal times advance by a_k Delta (Eq. 15); the fired channel
-                // lands exactly on its firing internal time and draws the next
-                const uint32_t n_mu = atomicAdd(&cnt[mu * 256], 1u) + 1u;
+                // lands exactly on its firing internal time and takes its next
+                // draw: the one just made when it fires twice in a row
+                next_draw[mu_p * 256u] = E_new;
+                const double E = mu == mu_p ? E_new : E_old;
 #pragma unroll
                 for (int k = 0; k < MT; ++k) T[k] = fma(a[k], d1, T[k]);
-                const uint64_t m = rt_block_m53(
-                    rt_philox_traj(tw, n_mu >> 1, (uint32_t)mu, net_k1, key0, key1), n_mu);
-                const double E = rt_neglog_wave(m, false, &ws->slow_logs, sc);
 #pragma unroll
                 for (int k = 0; k < MT; ++k)
-                    if (f[k]) {
-                        asm volatile("");
-                        T[k] = Pk[k];
-                        Pk[k] = Pk[k] + E;
+                    if (__builtin_amdgcn_inverse_ballot_w64(fm[k])) {
+                        rt_land(T[k], Pk[k], E);
 #pragma unroll
                         for (int j = 0; j < NT; ++j) X[j] += nu[k][j];
                     }
+                mu_p = mu;
+                n_next = atomicAdd(&cnt[mu * 256u], 1u) + 2u;
             } else {
-                atomicAdd(&cnt[mu * 256], 1u);
+                E_now = E_new;
+                u_now = u_new;
+                atomicAdd(&cnt[mu * 256u], 1u);
 #pragma unroll
                 for (int k = 0; k < MT; ++k)
-                    if (f[k]) {
-                        asm volatile("");
+                    if (__builtin_amdgcn_inverse_ballot_w64(fm[k])) {
+                        asm volatile("");              // (keeps the mask: no selects)
 #pragma unroll
                         for (int j = 0; j < NT; ++j) X[j] += nu[k][j];
                     }
@@ -620,7 +713,8 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
             refresh();
             if (__builtin_expect(__ballot(fired >= C.max_firings) != 0ull, 0)) {
                 capped = fired >= C.max_firings;
-                t_stop = capped ? -1.0 : t_stop;
+                t_stop = capped ? -1.0 : t_stop;               // (ends without its event)
+                s_next = capped ? __builtin_inf() : s_next;
             }
         }
     }
@@ -674,32 +768,51 @@ __global__ void rt_setup_kernel(rt_ws* ws, unsigned long long* extra, int64_t n_
 typedef void (*thread_kernel_t)(rt_class_dev);
 
 template <int MT, int NT>
-int launch_mn(const rt_class_dev& C, int block, int grid, hipStream_t stream, int* grid_used,
+int launch_mn(rt_class_dev C, int* block, int grid, hipStream_t stream, int* grid_used,
               int64_t lanes_wanted, int method, bool sched)
 {
     thread_kernel_t kfn = method == RTSSA_METHOD_DIRECT
                               ? rt_thread_kernel<MT, NT, RTSSA_METHOD_DIRECT, false>
                               : (sched ? rt_thread_kernel<MT, NT, RTSSA_METHOD_RANDOM_TIME, true>
                                        : rt_thread_kernel<MT, NT, RTSSA_METHOD_RANDOM_TIME, false>);
-    if (grid <= 0) {
-        int dev = 0, cus = 0, per_cu = 0;
+    C.lanes = 64;
+    int dev = 0, cus = 0;
+    if (grid <= 0 || *block <= 0)
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return rt_fail(RTSSA_E_HIP, "device query failed");
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, block, 0) != hipSuccess ||
+    if (*block <= 0) {
+        *block = 256;
+        if (grid <= 0 && !C.exclusive && lanes_wanted <= 6 * (int64_t)cus) {
+            // A small ensemble: single wavefronts of few lanes on three quarters
+            // of the CUs.  A firing's latency bounds it, and a wavefront waits
+            // for every lane's rare events, so fewer lanes are faster while each
+            // wavefront has its CU to itself (Lotka-Volterra, 256 / 1000 / 2000
+            // trajectories: 7.0 / 7.0 / 3.8 ms in workgroups of 256 full lanes,
+            // 4.7 / 5.1 / 3.2 ms at 2, 6 and 11 lanes; 8.8 ms for 1000 one-lane
+            // wavefronts, four to a CU; from 8000 trajectories on full
+            // wavefronts are as fast).
+            *block = 64;
+            C.lanes = (int32_t)std::max<int64_t>(1, (4 * lanes_wanted + 3 * cus - 1) / (3 * cus));
+        }
+    }
+    if (grid <= 0) {
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, *block, 0) != hipSuccess ||
             per_cu < 1)
             per_cu = 1;
-        int64_t need = (lanes_wanted + block - 1) / block;
-        int64_t full = (int64_t)cus * per_cu;
+        const int64_t per_block = (int64_t)(*block / 64) * C.lanes;
+        const int64_t need = (lanes_wanted + per_block - 1) / per_block;
+        const int64_t full = (int64_t)cus * per_cu;
         grid = (int)std::max<int64_t>(1, std::min<int64_t>(need, full));
     }
     if (grid_used) *grid_used = grid;
-    hipLaunchKernelGGL(kfn, dim3(grid), dim3(block), 0, stream, C);
+    hipLaunchKernelGGL(kfn, dim3(grid), dim3(*block), 0, stream, C);
     return hipGetLastError() == hipSuccess ? RTSSA_OK : rt_fail(RTSSA_E_HIP, "thread kernel launch failed");
 }
 
 template <int MT>
-int launch_m(int N, const rt_class_dev& C, int block, int grid, hipStream_t stream, int* gu,
+int launch_m(int N, const rt_class_dev& C, int* block, int grid, hipStream_t stream, int* gu,
              int64_t lanes, int method, bool sched)
 {
     if (N <= 1) return launch_mn<MT, 1>(C, block, grid, stream, gu, lanes, method, sched);
@@ -716,8 +829,9 @@ int rt_thread_supported(int M, int N)
 }
 
 // M and N are the largest of the class (the kernel pads with dead channels
-// and absent species); lanes = trajectories wanted in flight.
-int rt_launch_thread(int M, int N, const rt_class_dev& C, int block, int grid,
+// and absent species); lanes = trajectories wanted in flight; *block <= 0 is
+// set to the workgroup size chosen.
+int rt_launch_thread(int M, int N, const rt_class_dev& C, int* block, int grid,
                      hipStream_t stream, int* grid_used, int64_t lanes, int method)
 {
     const bool sched = C.has_schedule != 0;
@@ -725,8 +839,7 @@ int rt_launch_thread(int M, int N, const rt_class_dev& C, int block, int grid,
         return rt_fail(RTSSA_E_UNSUPPORTED, "rate schedules run with the random-time method");
     if (!rt_thread_supported(M, N))
         return rt_fail(RTSSA_E_UNSUPPORTED, "network too large for the thread mapping");
-    if (block <= 0) block = 256;
-    if (block > 256 || block % 64)
+    if (*block > 256 || *block % 64)
         return rt_fail(RTSSA_E_INVALID, "thread mapping block must be a multiple of 64, <= 256");
     switch (M) {
         case 0:
