@@ -78,7 +78,7 @@ int rt_launch_class(int mapping, int max_M, int max_N, int max_nu, const rt_clas
         if (max_M > 8 * L) return rt_fail(RTSSA_E_UNSUPPORTED, "too many channels for this lane count");
         if (max_nu > L) return rt_fail(RTSSA_E_UNSUPPORTED, "a reaction changes more species than lanes");
         *block_used = L;
-        return rt_launch_subwave(max_M, C, L, grid, stream, grid_used);
+        return rt_launch_subwave(max_M, C, L, grid, lanes, stream, grid_used);
     }
     if (mapping == RTSSA_MAP_WORKGROUP) {
         int L = block > 0 ? block : rt_auto_group_size(max_M);
@@ -177,7 +177,7 @@ int rt_run_rows(const rtssa_network* net, const rtssa_options& o)
     const int mapping = o.mapping == RTSSA_MAP_AUTO ? rt_auto_mapping(net) : o.mapping;
     // (also for M = 0: the kernels load the rows of channel 0 before they
     // find that nothing can fire, and the tables then hold one empty row)
-    return mapping == RTSSA_MAP_WORKGROUP ? 2 : (mapping == RTSSA_MAP_WAVE ? 1 : 0);
+    return mapping == RTSSA_MAP_WORKGROUP || mapping == RTSSA_MAP_WAVE ? 2 : 0;
 }
 
 bool rt_rows_ready(const rtssa_network* net, int rows)

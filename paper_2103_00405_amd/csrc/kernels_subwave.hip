@@ -2,18 +2,34 @@
 // trajectories per wavefront, for mid-size networks.
 //
 // Channel k of a trajectory belongs to lane k mod L of its group, slot k / L;
-// T_k, P_k, a_k and 1/a_k live in that lane's VGPRs (slots past the
-// network's M are frozen channels that never win).  Each group has its own
-// species counts X, firing counts n_k and one stale word per lane (bit s:
-// slot s must recompute its propensity) in LDS.  The groups of a
-// wavefront advance in lockstep, one firing per pass, but each group runs its
-// own trajectory: the expensive per-firing tail (one Philox block and one
-// correctly rounded logarithm for the fired channel, Eq. 26) runs in one lane
-// per group, so a wavefront pays it once for 64 / L firings, and it runs
-// while the fired channel's fixed-stride rows (its jump and the channels of
-// D(mu), the lazy form's rows) load in one round trip.  There are no
-// workgroup barriers: a group lives inside one wavefront, whose LDS accesses
-// complete in program order.
+// T_k and P_k live in that lane's VGPRs (slots past the network's M are frozen
+// channels that never win).  LDS holds, per wavefront and slot, a_k, a
+// binary32 1 / a_k, the channel's next draw E(k, n_k + 1) and n_k, at
+// [slot][lane] (no bank conflicts), and each group's species counts X.  The
+// groups of a wavefront advance in lockstep, one firing per pass, each with its
+// own trajectory.  There are no workgroup barriers: a group lives inside one
+// wavefront, whose LDS accesses complete in program order.
+//
+// One firing (section 4, Table 2, in the internal-time form of Eq. 14-16):
+//   selection  the gaps (P_k - T_k) / a_k in binary32, the channel index in
+//              their low bits, so that one 32-bit minimum per lane exchange
+//              finds both (Eq. 25); the winner's exact gap from one reciprocal.
+//              Where the second smallest is within 2^-12 of the smallest, or a
+//              value is not a plain positive number, the exact binary64
+//              selection with second minimum runs instead;
+//   rows       mu's fixed-stride rows in one round trip: its jump and the
+//              records of the channels D(mu) (Gibson & Bruck's dependency
+//              graph, cited in section 5), each with its reactants, rate and
+//              the reactants' changes under v_mu; while they load, waiting
+//              draws are made, one slot per lane, when 16 lanes have one or a
+//              group's mu fires before its draw is there;
+//   event      T_k += a_k Delta, T_mu = P_mu, P_mu += E (Eq. 15, 26), new a_k
+//              of D(mu) by the lanes holding its records, X + v_mu.
+// Measured (45 channels, 20000 trajectories, with the score gradient: 9.7 ms
+// before, 4.3 ms; 301 channels, 4000 trajectories: 44.8, 19.4 ms) against the
+// kernel this replaced, which kept a_k and 1 / a_k in registers, refreshed them
+// one stale slot at a time from the network tables, reduced (gap, second gap,
+// channel) in binary64 and made each draw in one lane a group.
 //
 // Work units are trajectories of the class's items, taken from a device
 // counter by one lane per group; every rare event (start or end of a
@@ -21,8 +37,8 @@
 // firing cap) is handled in a branch entered only when some group needs it.
 // With piecewise-constant rates (SCHED, Eq. 28), a rate breakpoint passed by
 // a group's next firing is one more such event: the group's clocks run to the
-// breakpoint at the old rates (a pending event with no fired channel) and
-// every slot turns stale, so the next pass takes the new rates.
+// breakpoint at the old rates, every propensity takes the new ones, and the
+// pass is repeated.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -31,164 +47,215 @@
 
 namespace {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = 128;
 
-// Waves per SIMD the register allocation must allow: 2.  With 8 slots of
-// channel state, the fired channel's rows and its early draw, 3 waves would
-// spill to scratch (40-80 bytes per lane); at 2 the classes of 9-64 and
-// 65-128 channels of a 4096-network batch ran 20 and 15 % faster alone, the
-// 129-256 class 5 % slower.
-constexpr int subwave_min_waves(int, bool) { return 2; }
+// Draws are made once this many lanes of a wavefront wait for one.
+constexpr int kDrawLanes = 16;
+
+// Waves per SIMD the register allocation must allow (LDS allows 3 at 6 slots
+// and 2 at 8).
+constexpr int subwave_min_waves(int S, bool SCHED) { return S <= 4 ? 4 : 3; }
+
+__device__ __forceinline__ int32_t med3_i32(int32_t a, int32_t b, int32_t c)
+{
+    int32_t r;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// Smallest value over aligned groups of W lanes, in every lane.
+template <int W>
+__device__ __forceinline__ int32_t group_min_i32(int32_t v)
+{
+    if (W >= 2) v = min(v, rt_dpp<0xB1>(v));       // quad_perm [1,0,3,2]
+    if (W >= 4) v = min(v, rt_dpp<0x4E>(v));       // quad_perm [2,3,0,1]
+    if (W >= 8) v = min(v, rt_dpp<0x141>(v));      // row_half_mirror
+    if (W >= 16) v = min(v, rt_dpp<0x140>(v));     // row_mirror
+    uint32_t p, q;
+    if (W >= 32) {
+        rt_swap<16>((uint32_t)v, p, q);
+        v = min((int32_t)p, (int32_t)q);
+    }
+    if (W >= 64) {
+        rt_swap<32>((uint32_t)v, p, q);
+        v = min((int32_t)p, (int32_t)q);
+    }
+    return v;
+}
+
+__device__ __forceinline__ bool plain_rate(double c)
+{
+    return c == 0.0 || (c >= 0x1p-100 && c <= 0x1p60);
+}
+
+// LDS bytes of one wavefront: per slot and lane a_k, the next draw, 1 / a_k
+// and n_k; then X of each group.
+constexpr size_t wave_lds_bytes(int L, int S, int NP)
+{
+    return (size_t)S * 64 * 24 + (size_t)(64 / L) * NP * 4;
+}
 
 template <int L, int S, bool SCHED>
 __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwave_kernel(rt_class_dev C)
 {
+    constexpr int G = 64 / L;                              // groups of a wavefront
+    constexpr int LOG2L = __builtin_ctz(L);
+    constexpr int32_t kKey = 8 * L - 1;                    // channel bits of a selection key
     constexpr unsigned long long kGroupBits = L == 64 ? ~0ull : ((1ull << L) - 1ull);
     rt_ws* const ws = C.ws;
     // Issue priority over other kernels' wavefronts sharing a CU (batches):
     // below the thread mapping's, above the lazy and workgroup kernels'.
     __builtin_amdgcn_s_setprio(2);
     const uint32_t key0 = ws->key0, key1 = ws->key1;
-    const int tid = threadIdx.x, li = tid % L, lane = tid & 63;
-    const unsigned long long gmask = kGroupBits << (lane - li);
-    extern __shared__ int32_t dyn_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, li = lane % L, gbase = lane - li;
+    const unsigned long long gmask = kGroupBits << gbase;
+    extern __shared__ __align__(16) char dyn_lds[];
     __shared__ rt_log_lds<kBlock / 64> log_lds;
     const auto sc = log_lds.init();
-    constexpr int LOG2L = __builtin_ctz(L);
-    const int NP = (C.max_N + 3) & ~3, MP = (C.max_M + 3) & ~3;
-    int32_t* X = dyn_lds + (tid / L) * (NP + L + MP);   // [N] species counts
-    uint32_t* stale_w = (uint32_t*)(X + NP);            // [L] stale words
-    uint32_t* nk = stale_w + L;                         // [M] firing counts
+    const int NP = (C.max_N + 3) & ~3;
+    // this lane's slots: entry s 64 of each array
+    double* const la = (double*)(dyn_lds + (tid >> 6) * wave_lds_bytes(L, S, NP)) + lane;
+    double* const le = la + S * 64;
+    float* const linv = (float*)(le - lane + S * 64) + lane;
+    uint32_t* const lnk = (uint32_t*)(linv + S * 64);
+    int32_t* const X = (int32_t*)(lnk - lane + S * 64) + (lane / L) * NP;
+    // offset from this lane's entries to channel k's of its group
+    auto at = [&](int k) { return ((k >> LOG2L) << 6) + (k & (L - 1)) - li; };
     const rt_cptr<int64_t> unit_start = rt_const(C.unit_start);
     const int64_t total = unit_start[C.count];
 
     // channel state of this lane's slots
-    double T[S], Pk[S], a[S], inv[S];
+    double T[S], P[S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) { T[s] = 0.0; Pk[s] = 0.0; a[s] = 0.0; inv[s] = __builtin_inf(); }
+    for (int s = 0; s < S; ++s) { T[s] = 0.0; P[s] = __builtin_inf(); }
     // trajectory context (identical in every lane of the group)
     rt_cptr<rt_item_dev> it = rt_const(C.items);
-    int M = 0, N = 0, mu = 0;
+    int M = 0, N = 0;
     int64_t r = 0;
     uint32_t traj = 0, net_id = 0, fired = 0, tie = kTieNone;
-    double t = 0.0, t_end = 0.0, s_next = 0.0, delta = 0.0, E = 0.0;
+    double t = 0.0, t_end = 0.0, s_next = 0.0;
     int32_t g = 0;
     unsigned long long hash = kFnvOffset;
-    bool active = true, fresh = true, capped = false, pending = false;
+    bool active = lane / L < C.lanes, fresh = true, capped = false;
+    uint32_t waiting = 0u;                                 // slots whose next draw is not made yet
+    float g_min = 1e-30f;                                  // smallest gap the binary32 order takes
     // rate schedule: breakpoints passed, and the next one
     int32_t piece = 0;
     double b_next = __builtin_inf();
+    // a fresh group passes through its first pass with defined values
+#pragma unroll
+    for (int s = 0; s < S; ++s) { la[s * 64] = 0.0; linv[s * 64] = __builtin_inff(); }
+    rt_wave_lds_fence();
 
-    while (__ballot(active) != 0ull) {
-        if (!active) continue;
+    while (active) {
         const rt_cptr<rt_net_dev> net = &it->net;
-        // ---- pass over own channels: apply the pending event, refresh, gap
-        if (pending) {
-            // every internal clock advances by a_k delta (Eq. 15) ...
-#pragma unroll
-            for (int s = 0; s < S; ++s) T[s] = fma(a[s], delta, T[s]);
-            // ... except the fired one: its firing time, then the next (Eq. 26);
-            // mu < 0 after a rate breakpoint
-            if ((!SCHED || mu >= 0) && li == (mu & (L - 1))) {
-                const int sm = mu >> LOG2L;
-#pragma unroll
-                for (int s = 0; s < S; ++s) {
-                    const bool f = s == sm;
-                    T[s] = f ? Pk[s] : T[s];
-                    Pk[s] = f ? Pk[s] + E : Pk[s];
-                }
-            }
-            // the pending event's stale bits for this lane (read and cleared;
-            // the pass then runs with pending = false if it is repeated)
-            unsigned int stale = stale_w[li];
-            stale_w[li] = 0u;
-            pending = false;
-            // rates in force: c before the first breakpoint, row i of the
-            // schedule from breakpoint i on
-            const rt_cptr<double> crate =
-                SCHED && piece > 0 ? rt_const(net->sched_c) + (size_t)(piece - 1) * M
-                                   : rt_const(net->c);
-            // refresh one stale slot at a time (rare; keeps the code and the
-            // register footprint of the propensity out of the unrolled pass)
-            while (stale) {
-                const int s1 = __builtin_ctz(stale);
-                stale &= stale - 1u;
-                const int k = li + s1 * L;
-                const double an = rt_propensity_mem(rt_const(net->react)[k], crate[k], X);
-                const double in = 1.0 / an;
-#pragma unroll
-                for (int s = 0; s < S; ++s) {
-                    a[s] = s == s1 ? an : a[s];
-                    inv[s] = s == s1 ? in : inv[s];
-                }
-            }
-        }
-        rt_min2 loc = rt_min2_empty();
+        // ---- selection
+        double df[S];
+        int32_t k1 = 0x7FFFFFFF, k2 = 0x7FFFFFFF;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-            const double raw = (Pk[s] - T[s]) * inv[s];
-            const double d = a[s] == 0.0 ? __builtin_inf() : fmax(raw, 0.0);
-            rt_min2_push(loc, d, s);                       // slot now, channel below
+            df[s] = P[s] - T[s];
+            const float gap = (float)df[s] * linv[s * 64];
+            const int32_t key = (int32_t)rt_and_or(__float_as_uint(gap), (uint32_t)~kKey,
+                                                   (uint32_t)(s * L + li));
+            k2 = med3_i32(k1, k2, key);
+            k1 = min(k1, key);
         }
-        loc = rt_min2_slot_to_channel(loc, li, LOG2L);
-        // ---- argmin across the group's lanes (lowest k wins ties)
-        loc = rt_min2_allreduce<L>(loc);
-        const double d1 = loc.d1, d2 = loc.d2;
-        const int kmin = loc.k;
+        const int32_t kbest = group_min_i32<L>(k1);
+        int mu = kbest & kKey;
+        // rare: the second smallest is close (a lane's candidate: its smallest,
+        // or its second where it owns mu), or the smallest is no plain number
+        const float gap1 = __uint_as_float((uint32_t)(kbest & ~kKey));
+        const int32_t reach = __float_as_int(gap1 * (1.0f + 0x1p-12f)) | kKey;
+        const bool amb = !(gap1 > g_min) | ((k1 == kbest ? k2 : k1) <= reach);
+        // the winner's exact gap, from its owner lane's P - T
+        double dm = df[0];
+#pragma unroll
+        for (int s = 1; s < S; ++s) dm = (mu >> LOG2L) == s ? df[s] : dm;
+        const double a_mu = la[at(mu)];
+        dm = __shfl(dm, gbase + (mu & (L - 1)), 64);
+        double d1 = dm * rt_recip(a_mu);
+        bool near = false, clamped = false;
+        const unsigned long long ambs = __ballot(amb);
+        if (__builtin_expect(ambs != 0ull, 0)) {
+            if ((ambs & gmask) != 0ull) {
+                // the exact form: max(0, RN((P - T) RN(1 / a))), +inf for a
+                // frozen channel, lowest k on ties, second minimum
+                rt_min2 loc = rt_min2_empty();
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const double a = la[s * 64];
+                    const double raw = df[s] * (1.0 / a);
+                    rt_min2_push(loc, a == 0.0 ? __builtin_inf() : fmax(raw, 0.0), s);
+                }
+                loc = rt_min2_slot_to_channel(loc, li, LOG2L);
+                loc = rt_min2_allreduce<L>(loc);
+                d1 = loc.d1;
+                mu = loc.k == 0x7FFFFFFF ? 0 : loc.k;
+                near = rt_near_tie(loc.d1, loc.d2);
+                // a zero gap: was it clamped from a negative raw gap?
+                if (d1 == 0.0 && li == (mu & (L - 1))) {
+#pragma unroll
+                    for (int s = 0; s < S; ++s)
+                        if ((mu >> LOG2L) == s) clamped = df[s] * (1.0 / la[s * 64]) < 0.0;
+                }
+            }
+        }
         const double t_new = t + d1;
-        const bool absorbed = d1 == __builtin_inf();
+        const bool own = li == (mu & (L - 1));
+        const int sm = mu >> LOG2L;
+        // ---- mu's rows, one round trip: its jump (lane li < nu_stride: entry
+        // li) and the first records (lane li: record li, then li + L); a mu
+        // that does not fire (or is none) has rows as well
+        constexpr int kR = G > 1 ? 2 : 1;
+        const int mr = M > 0 ? min(mu, M - 1) : 0;
+        const int nu_stride = net->nu_stride;
+        const int n_other = rt_const(net->touch)[mr * 64];
+        const int2 nv = rt_const(net->nu_fixed)[mr * nu_stride + min(li, nu_stride - 1)];
+        int4 rec[kR];
+        double rc[kR];
+        int2 rd[kR];
+#pragma unroll
+        for (int q = 0; q < kR; ++q) {
+            rec[q] = rt_const(net->grow)[mr * 64 + li + q * L];
+            rc[q] = rt_const(net->growc)[mr * 64 + li + q * L];
+            rd[q] = rt_const(net->gdel)[mr * 64 + li + q * L];
+        }
         const bool live = !fresh && !capped;
+        // ---- draws while the rows load
+        const bool need = live && own && ((waiting >> sm) & 1u);
+        const unsigned long long waiters = __ballot(waiting != 0u);
+        if (__ballot(need) != 0ull || __popcll(waiters) >= kDrawLanes) {
+            if (waiting != 0u) {
+                const int s1 = need ? sm : __builtin_ctz(waiting);
+                const uint32_t n1 = lnk[s1 * 64] + 1u;
+                le[s1 * 64] = rt_exp1_wave(key0, key1, traj, net_id, (uint32_t)(s1 * L + li), n1,
+                                           &ws->slow_logs, sc);
+                waiting &= ~(1u << s1);
+            }
+        }
+        const bool absorbed = d1 == __builtin_inf();
         // the next firing would come after a rate breakpoint (Eq. 28)
         const bool brk = SCHED && live && b_next < t_end && t_new > b_next;
         const bool term = !brk && (absorbed || t_new > t_end);
         const bool event = live && !term && !brk;
-        // ---- the fired channel's fixed-stride rows, one round trip: its jump
-        // (lane li < nu_stride: entry li) and its touch row (lane li: the 64 / L
-        // consecutive entries from li 64 / L; entry 0 counts the channels of
-        // D(kmin) other than kmin, entries 1..63 name them, -1 past the end)
-        constexpr int kTE = 64 / L;                         // touch entries per lane
-        const int kr = event ? kmin : 0;                    // row 0 exists (M >= 1)
-        const int nu_stride = net->nu_stride;
-        const int2 nv = rt_const(net->nu_fixed)[kr * nu_stride + min(li, nu_stride - 1)];
-        int32_t tch[kTE];
-        {
-            const rt_cptr<int32_t> row = rt_const(net->touch) + (size_t)kr * 64 + li * kTE;
-#pragma unroll
-            for (int e = 0; e < kTE; ++e) tch[e] = row[e];
-        }
-        // the fired channel's next Exp(1) (Eq. 26) in its owner lane, while
-        // the rows load (discarded if the event is not applied in this pass)
-        uint32_t nm_new = 0;
-        double E_new = 0.0;
-        bool slow_new = false;                              // counted when applied
-        if (event && li == (kmin & (L - 1))) {
-            nm_new = nk[kmin] + 1u;
-            E_new = rt_neglog_wave(rt_draw_m53(key0, key1, traj, net_id, (uint32_t)kmin, nm_new),
-                                   false, nullptr, sc, &slow_new);
-        }
         // ---- the jump v_mu, checked against [0, 2^31 - 1] by lanes < |v_mu|
-        int32_t xv = 0, xs = 0;
-        bool okl = true;
         const bool has_nu = event && li < nu_stride && nv.x >= 0;
-        if (has_nu) {
-            xs = nv.x;
-            const int64_t v = (int64_t)X[xs] + nv.y;
-            okl = v >= 0 && v <= 0x7FFFFFFF;
-            xv = (int32_t)v;
-        }
-        const bool ok = (__ballot(!okl) & gmask) == 0ull;
-        const bool near_tie = event && rt_near_tie(d1, d2);
-        // a zero gap may have been clamped from a negative raw gap
-        const bool rare =
-            !live || term || near_tie || d1 == 0.0 || !ok || s_next < t_new || brk;
-        if (__builtin_expect(__ballot(rare) != 0ull, 0)) {
+        int64_t xv = 0;
+        if (has_nu) xv = (int64_t)X[nv.x] + nv.y;
+        const bool okl = xv >= 0 && xv <= 0x7FFFFFFF;
+        // (in all these tests a frozen or unstarted group counts as rare)
+        const unsigned long long bad = __ballot(!okl);
+        const bool rare = !live || !(t_new <= t_end) || near || clamped || s_next < t_new || brk;
+        if (__builtin_expect((__ballot(rare) | bad) != 0ull, 0)) {
+            const bool ok = (bad & gmask) == 0ull;
+            const bool near_tie = event && near;
             // Counted once per event: when another group of the wavefront
             // stops or meets a breakpoint, this group repeats its pass below
             // without applying its event, so the counters are bumped only once
             // the event is known to be applied (or, for a near-tie, when the
             // event ends the trajectory by an overflow, as the oracle counts
             // it); tie and the samples are idempotent.
-            bool clamped = false;
             if (event) {
                 if (near_tie) tie = tie == kTieNone ? fired : tie;
                 while (s_next < t_new) {
@@ -198,12 +265,6 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
                     }
                     ++g;
                     s_next = g < it->G ? rt_const(it->s)[g] : __builtin_inf();
-                }
-                if (ok && d1 == 0.0 && li == (kmin & (L - 1))) {
-                    const int sm = kmin >> LOG2L;
-#pragma unroll
-                    for (int s = 0; s < S; ++s)
-                        clamped = s == sm ? (Pk[s] - T[s]) * inv[s] < 0.0 : clamped;
                 }
             }
             const bool stop = !live || term || !ok;
@@ -225,8 +286,8 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
                 for (int s = 0; s < S; ++s) {
                     const int k = li + s * L;
                     if (k < M) {
-                        if (good) T[s] = fma(a[s], dt, T[s]);
-                        if (it->n_out) it->n_out[r * M + k] = nk[k];
+                        if (good) T[s] = fma(la[s * 64], dt, T[s]);
+                        if (it->n_out) it->n_out[r * M + k] = lnk[s * 64];
                         if (it->T_out) it->T_out[r * M + k] = T[s];
                     }
                 }
@@ -245,11 +306,10 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
                 // ---- take the next trajectory unit
                 unsigned long long u = 0;
                 if (li == 0) u = atomicAdd(&ws->next_unit, 1ull);
-                u = __shfl(u, lane - li, 64);
-                rt_wave_lds_fence();                          // X and flags are reused
+                u = __shfl(u, gbase, 64);
+                rt_wave_lds_fence();                          // X is reused
                 fresh = false;
                 capped = false;
-                pending = false;
                 active = (int64_t)u < total;
                 if (active) {
                     const int item = rt_find_item(unit_start, C.count, (int64_t)u);
@@ -262,8 +322,6 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
                     traj = it->traj_offset + (uint32_t)r;
                     const int32_t* x0 = it->x0 + (it->x0_per_traj ? r * N : 0);
                     for (int j = li; j < N; j += L) X[j] = x0[j];
-                    for (int k = li; k < M; k += L) nk[k] = 0u;
-                    stale_w[li] = 0u;
                     t = 0.0;
                     g = 0;
                     s_next = it->G > 0 ? rt_const(it->s)[0] : __builtin_inf();
@@ -273,48 +331,63 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
                     fired = 0;
                     tie = kTieNone;
                     hash = kFnvOffset;
+                    waiting = 0u;
                     rt_wave_lds_fence();
-#pragma unroll
-                    for (int s = 0; s < S; ++s) {
-                        T[s] = 0.0;
-                        Pk[s] = 0.0;
-                        a[s] = 0.0;
-                        inv[s] = __builtin_inf();
-                    }
-                    // first internal firing times and propensities, one slot at a time
+                    // first internal firing times E(k, 0) and next draws E(k, 1)
+                    // (the two words of one block) and propensities, one slot at
+                    // a time; a slot past M keeps P = +inf, a = 0
+                    bool plain = true;
 #pragma unroll 1
                     for (int s1 = 0; s1 < S; ++s1) {
                         const int k = li + s1 * L;
+                        double p0 = __builtin_inf(), an = 0.0;
                         if (k < M) {
-                            const double p0 = rt_exp1_wave(key0, key1, traj, net_id, (uint32_t)k,
-                                                           0u, &ws->slow_logs, sc);
-                            const double an = rt_propensity_mem(rt_const(it->net.react)[k],
-                                                            rt_const(it->net.c)[k], X);
-                            const double in = 1.0 / an;
+                            const rt_u4 w =
+                                rt_philox4x32_10(rt_u4{0u, (uint32_t)k, traj, net_id}, key0, key1);
+                            p0 = rt_neglog_wave((((uint64_t)w.y << 32) | w.x) >> 11, false,
+                                                &ws->slow_logs, sc);
+                            le[s1 * 64] = rt_neglog_wave((((uint64_t)w.w << 32) | w.z) >> 11, false,
+                                                         &ws->slow_logs, sc);
+                            const double c = rt_const(it->net.c)[k];
+                            an = rt_propensity_mem(rt_const(it->net.react)[k], c, X);
+                            plain = plain && plain_rate(c);
+                        }
+                        la[s1 * 64] = an;
+                        linv[s1 * 64] = __builtin_amdgcn_rcpf((float)an);
+                        lnk[s1 * 64] = 0u;
 #pragma unroll
-                            for (int s = 0; s < S; ++s) {
-                                Pk[s] = s == s1 ? p0 : Pk[s];
-                                a[s] = s == s1 ? an : a[s];
-                                inv[s] = s == s1 ? in : inv[s];
-                            }
+                        for (int s = 0; s < S; ++s) {
+                            P[s] = s == s1 ? p0 : P[s];
+                            T[s] = 0.0;
                         }
                     }
+                    g_min = (__ballot(!plain) & gmask) ? __builtin_inff() : 1e-30f;
+                    rt_wave_lds_fence();
                 }
             }
             if (SCHED && brk) {
                 // the clocks run to the breakpoint at the old rates, then
                 // every propensity takes the new ones
-                delta = b_next - t;
+                const double db = b_next - t;
+                const rt_cptr<double> cr = rt_const(net->sched_c) + (size_t)piece * M;
                 t = b_next;
                 ++piece;
                 b_next = piece < net->sched_B ? rt_const(net->sched_t)[piece]
                                               : __builtin_inf();
-                uint32_t all = 0u;
+                bool plain = true;
 #pragma unroll
-                for (int s = 0; s < S; ++s) all |= li + s * L < M ? 1u << s : 0u;
-                stale_w[li] = all;
-                mu = -1;
-                pending = true;
+                for (int s = 0; s < S; ++s) {
+                    const int k = li + s * L;
+                    T[s] = fma(la[s * 64], db, T[s]);
+                    if (k < M) {
+                        const double an = rt_propensity_mem(rt_const(net->react)[k], cr[k], X);
+                        la[s * 64] = an;
+                        linv[s * 64] = __builtin_amdgcn_rcpf((float)an);
+                        plain = plain && plain_rate(cr[k]);
+                    }
+                }
+                g_min = (__ballot(!plain) & gmask) ? __builtin_inff() : 1e-30f;
+                rt_wave_lds_fence();
             }
             // started groups compute first gaps, groups past a breakpoint
             // solve again; the others repeat their (idempotent) pass
@@ -323,39 +396,64 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
             if (near_tie && li == 0) atomicAdd(&ws->near_ties, 1ull);
             if (clamped) atomicAdd(&ws->clamps, 1ull);
         }
-        // ---- the event: jump, dependency flags, fresh draw by the owner lane
-        mu = kmin;
-        if (has_nu) X[xs] = xv;
-        // stale bits: mu itself (its propensity may read a species it
-        // changes) and the channels of its touch row
-        if (li == 0) atomicOr(&stale_w[mu & (L - 1)], 1u << (mu >> LOG2L));
+        // ---- the event: internal clocks, the fired channel's next draw
 #pragma unroll
-        for (int e = 0; e < kTE; ++e) {
-            const int kk = tch[e];
-            if (li * kTE + e > 0 && kk >= 0) atomicOr(&stale_w[kk & (L - 1)], 1u << (kk >> LOG2L));
+        for (int s = 0; s < S; ++s) T[s] = fma(la[s * 64], d1, T[s]);
+        if (own) {
+            const double E = le[sm * 64];
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+                if (sm == s) rt_land(T[s], P[s], E);
+            lnk[sm * 64] += 1u;
+            waiting |= 1u << sm;
         }
-        {
-            // more than 63 others: the rest of the CSR list D(mu) (rare)
-            const int n_other = __shfl(tch[0], lane - li, 64);
-            if (n_other > 63) {
-                const int de = rt_const(net->dep_ptr)[mu + 1];
-                for (int q = rt_const(net->touch_more)[mu] + li; q < de; q += L) {
-                    const int kk = rt_const(net->dep_idx)[q];
-                    atomicOr(&stale_w[kk & (L - 1)], 1u << (kk >> LOG2L));
-                }
+        // ---- new propensities of mu and D(mu) from the records: X before the
+        // jump plus the record's changes
+        auto touch = [&](const int4& e, double c, const int2& dl) {
+            if (e.x >= 0) {
+                const int kind = (int)((uint32_t)e.y >> 29);
+                int32_t v0 = 0, v1 = 0;
+                if (kind != RT_H_ZERO) v0 = X[e.y & RT_SPECIES_MASK] + dl.x;
+                if (kind == RT_H_TWO) v1 = X[e.z] + dl.y;
+                const double an = rt_propensity_counts(kind, (uint32_t)v0, (uint32_t)v1, c);
+                const int o = at(e.x);
+                la[o] = an;
+                linv[o] = __builtin_amdgcn_rcpf((float)an);
+            }
+        };
+        // (with a schedule the rates in force come from the piece)
+        const rt_cptr<double> crate =
+            SCHED && piece > 0 ? rt_const(net->sched_c) + (size_t)(piece - 1) * M
+                               : rt_const(net->c);
+#pragma unroll
+        for (int q = 0; q < kR; ++q)
+            touch(rec[q], SCHED ? crate[max(rec[q].x, 0)] : rc[q], rd[q]);
+        if constexpr (kR * L < 64) {
+            const int rows = min(n_other, 63) + 1;
+            for (int q = kR * L; q < rows; q += L) {
+                const int o = mr * 64 + q + li;              // (q + li < 64)
+                const int4 e = rt_const(net->grow)[o];
+                touch(e, SCHED ? crate[max(e.x, 0)] : rt_const(net->growc)[o],
+                      rt_const(net->gdel)[o]);
             }
         }
-        if (li == (mu & (L - 1))) {
-            nk[mu] = nm_new;
-            E = E_new;
-            if (slow_new) atomicAdd(&ws->slow_logs, 1ull);
-        }
+        if (has_nu) X[nv.x] = (int32_t)xv;
         rt_wave_lds_fence();
+        if (__builtin_expect(n_other > 63, 0)) {
+            // more than 63 others: the rest of the CSR list D(mu) (rare)
+            const int de = rt_const(net->dep_ptr)[mu + 1];
+            for (int q = rt_const(net->touch_more)[mu] + li; q < de; q += L) {
+                const int k = rt_const(net->dep_idx)[q];
+                const double an = rt_propensity_mem(rt_const(net->react)[k], crate[k], X);
+                const int o = at(k);
+                la[o] = an;
+                linv[o] = __builtin_amdgcn_rcpf((float)an);
+            }
+            rt_wave_lds_fence();
+        }
         t = t_new;
-        delta = d1;
         ++fired;
         hash = (hash ^ (unsigned long long)(uint32_t)mu) * kFnvPrime;
-        pending = true;
         capped = fired >= C.max_firings;
     }
 }
@@ -371,11 +469,11 @@ subwave_kernel_t sw_pick(bool sched)
 subwave_kernel_t select_subwave(int L, int S, bool sched)
 {
 #define RT_CASE(l, s) if (L == l && S == s) return sw_pick<l, s>(sched);
-    RT_CASE(4, 2) RT_CASE(4, 4) RT_CASE(4, 8)
-    RT_CASE(8, 4) RT_CASE(8, 8)
-    RT_CASE(16, 4) RT_CASE(16, 8)
-    RT_CASE(32, 4) RT_CASE(32, 8)
-    RT_CASE(64, 4) RT_CASE(64, 8)
+    RT_CASE(4, 2) RT_CASE(4, 4) RT_CASE(4, 6) RT_CASE(4, 8)
+    RT_CASE(8, 4) RT_CASE(8, 6) RT_CASE(8, 8)
+    RT_CASE(16, 4) RT_CASE(16, 6) RT_CASE(16, 8)
+    RT_CASE(32, 4) RT_CASE(32, 6) RT_CASE(32, 8)
+    RT_CASE(64, 4) RT_CASE(64, 6) RT_CASE(64, 8)
 #undef RT_CASE
     return nullptr;
 }
@@ -391,28 +489,38 @@ int rt_subwave_lanes(int M)
     return L;
 }
 
+// Slots per lane: the fewest of 2 (4 lanes only), 4, 6, 8 that hold M channels
+// (0: none).
 int rt_subwave_slots(int M, int L)
 {
-    int s = (M + L - 1) / L;
-    int p = 2;
-    while (p < s) p <<= 1;
-    if (L > 4 && p < 4) p = 4;
-    return p;
+    const int s = (M + L - 1) / L;
+    if (L == 4 && s <= 2) return 2;
+    return s <= 4 ? 4 : (s <= 6 ? 6 : (s <= 8 ? 8 : 0));
 }
 
-int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStream_t stream,
-                      int* grid_used)
+int rt_launch_subwave(int max_M, const rt_class_dev& C_, int L, int grid, int64_t units,
+                      hipStream_t stream, int* grid_used)
 {
+    rt_class_dev C = C_;
     const int S = rt_subwave_slots(max_M, L);
     subwave_kernel_t kfn = select_subwave(L, S, C.has_schedule != 0);
     if (!kfn) return rt_fail(RTSSA_E_UNSUPPORTED, "no sub-wave kernel for this size");
     const int NP = (C.max_N + 3) & ~3, MP = (C.max_M + 3) & ~3;
-    const size_t lds = (size_t)(kBlock / L) * (NP + L + MP) * 4;
-    if (lds > 64 * 1024) return rt_fail(RTSSA_E_UNSUPPORTED, "sub-wave LDS too large");
+    // the networks taken: X, one word per lane and one per channel of 256 lanes'
+    // groups within 64 KiB
+    if ((size_t)(256 / L) * (NP + L + MP) * 4 > 64 * 1024)
+        return rt_fail(RTSSA_E_UNSUPPORTED, "sub-wave LDS too large");
+    const size_t lds = (kBlock / 64) * wave_lds_bytes(L, S, NP);
+    if (lds > 48 * 1024 &&
+        hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds) != hipSuccess)
+        return rt_fail(RTSSA_E_HIP, "cannot raise the LDS limit");
+    C.lanes = 64 / L;
     if (grid <= 0) {
         int dev = 0, cus = 0, per_cu = 0;
-        hipGetDevice(&dev);
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            return rt_fail(RTSSA_E_HIP, "device query failed");
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, kBlock, lds) != hipSuccess ||
             per_cu < 1)
             per_cu = 1;

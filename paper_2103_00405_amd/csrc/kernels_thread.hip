@@ -97,14 +97,6 @@ __device__ __forceinline__ void propensities(const rt_term (&q)[MT], const doubl
     }
 }
 
-// A firing channel's internal times: T = P, then P += E.  In place (the
-// compiler adds into a temporary and copies) and never as selects.
-__device__ __forceinline__ void rt_land(double& T, double& P, double E)
-{
-    asm volatile("v_mov_b64 %0, %1" : "=v"(T) : "v"(P));
-    asm volatile("v_add_f64 %0, %0, %1" : "+v"(P) : "v"(E));
-}
-
 // (m + 1) 2^-53
 __device__ __forceinline__ double rt_u53(uint64_t m)
 {

@@ -98,6 +98,14 @@ __device__ __forceinline__ double rt_recip(double a)
     return fma(fma(-a, y, 1.0), y, y);
 }
 
+// A firing channel's internal times: T = P, then P += E.  In place (the
+// compiler adds into a temporary and copies) and never as selects.
+__device__ __forceinline__ void rt_land(double& T, double& P, double E)
+{
+    asm volatile("v_mov_b64 %0, %1" : "=v"(T) : "v"(P));
+    asm volatile("v_add_f64 %0, %0, %1" : "+v"(P) : "v"(E));
+}
+
 // The near-tie rule (Eq. 4 gives ties probability zero; in binary64 the two
 // smallest gaps d1 <= d2 can still round within reach of each other):
 // RN(d2 - d1) <= RN(1e-12 d1).
