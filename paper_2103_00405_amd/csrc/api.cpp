@@ -71,14 +71,14 @@ int rt_launch_class(int mapping, int max_M, int max_N, int max_nu, const rt_clas
     if (method != RTSSA_METHOD_RANDOM_TIME)
         return rt_fail(RTSSA_E_UNSUPPORTED, "the direct method runs only in the thread mapping");
     if (mapping == RTSSA_MAP_WAVE) {
-        int L = block > 0 ? block : rt_subwave_lanes(max_M);
+        int L = block > 0 ? block : rt_subwave_auto_lanes(max_M, lanes, 4);
         while (L < 64 && L < max_nu) L <<= 1;
         if (L != 4 && L != 8 && L != 16 && L != 32 && L != 64)
             return rt_fail(RTSSA_E_INVALID, "sub-wave lanes per trajectory must be 4..64, a power of 2");
         if (max_M > 8 * L) return rt_fail(RTSSA_E_UNSUPPORTED, "too many channels for this lane count");
         if (max_nu > L) return rt_fail(RTSSA_E_UNSUPPORTED, "a reaction changes more species than lanes");
         *block_used = L;
-        return rt_launch_subwave(max_M, C, L, grid, lanes, stream, grid_used);
+        return rt_launch_subwave(max_M, C, L, grid, stream, grid_used);
     }
     if (mapping == RTSSA_MAP_WORKGROUP) {
         int L = block > 0 ? block : rt_auto_group_size(max_M);

@@ -27,8 +27,9 @@ namespace {
 
 struct class_key {
     int mapping;    // RTSSA_MAP_*
-    int a, b;       // thread: padded (M, N); wave / workgroup: lanes per trajectory, 0;
-                    // tree methods: 64, the power-of-two channel range
+    int a, b;       // thread: padded (M, N); wave: lanes per trajectory, slot range;
+                    // workgroup: lanes per trajectory, 0; tree methods: 64, the
+                    // power-of-two channel range
     int method;     // RTSSA_METHOD_*: the tree methods have classes of their own
     // Class order is launch order.  The tree methods' classes (long, one
     // wavefront per trajectory) go first: launched after the others they
@@ -83,8 +84,13 @@ int tree_range(int M)
     return r;
 }
 
+// Wavefronts per CU that a batch's sub-wave trajectories may come to before
+// their lanes are chosen down: the uneven ones outlive the rest, so more lanes
+// pay for longer than in one even ensemble (4 there).
+constexpr int kBatchWavesPerCu = 16;
+
 class_key classify(const rtssa_network* net, int method, const std::vector<plan_entry>& plan,
-                   const rtssa_options& o)
+                   const rtssa_options& o, int64_t wave_units)
 {
     if (method != RTSSA_METHOD_RANDOM_TIME) return {RTSSA_MAP_WAVE, 64, tree_range(net->M), method};
     int mapping = o.mapping ? o.mapping : rt_auto_mapping(net);
@@ -95,9 +101,13 @@ class_key classify(const rtssa_network* net, int method, const std::vector<plan_
         mapping = RTSSA_MAP_WORKGROUP;
     if (mapping == RTSSA_MAP_WAVE) {
         int L = plan_lookup(plan, RTSSA_MAP_WAVE, net->M);
-        if (L <= 0) L = rt_subwave_lanes(net->M);
+        if (L <= 0) L = rt_subwave_auto_lanes(net->M, wave_units, kBatchWavesPerCu);
         while (L < 64 && (L < net->max_nu || L * 8 < net->M)) L <<= 1;
-        return {RTSSA_MAP_WAVE, L, 0, 0};
+        // two slot ranges a lane count: one class runs its small networks through
+        // the slots of its largest, a class per slot count leaves the graph more
+        // branches than the device has queues (192 / 400 / 800 random networks:
+        // one class 114 / 111 / 102 ms, two 103 / 98 / 108, four 89 / 126 / 118)
+        return {RTSSA_MAP_WAVE, L, rt_subwave_slots(net->M, L) <= 4 ? 4 : 8, 0};
     }
     int L = plan_lookup(plan, RTSSA_MAP_WORKGROUP, net->M);
     if (L <= 0) L = rt_auto_group_size(net->M);
@@ -182,10 +192,17 @@ static int batch_create(const rtssa_batch_item* items, int32_t count, const rtss
             }
         }
     }
+    // the sub-wave classes' lanes follow from how many trajectories share the
+    // device in that mapping
+    int64_t wave_units = 0;
+    for (int i = 0; i < count; ++i)
+        if (items[i].R > 0 && classify(items[i].net, items[i].method, plan, o, 0).mapping ==
+                                  RTSSA_MAP_WAVE && items[i].method == RTSSA_METHOD_RANDOM_TIME)
+            wave_units += items[i].R;
     std::map<class_key, std::vector<int>> groups;
     for (int i = 0; i < count; ++i) {
         if (items[i].R <= 0) continue;
-        const class_key key = classify(items[i].net, items[i].method, plan, o);
+        const class_key key = classify(items[i].net, items[i].method, plan, o, wave_units);
         if (key.method == RTSSA_METHOD_RANDOM_TIME &&
             (key.mapping == RTSSA_MAP_WORKGROUP || key.mapping == RTSSA_MAP_WAVE)) {
             // these kernels read the network's fixed-stride records

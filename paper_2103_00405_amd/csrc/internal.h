@@ -125,7 +125,7 @@ struct rt_class_dev {
     int32_t max_M;
     uint32_t max_firings;
     int32_t has_schedule;   // some item's network has a rate schedule
-    int32_t lanes;                     // thread mapping: trajectories a wavefront runs at once
+    int32_t lanes;          // thread mapping: trajectories a wavefront runs at once
 };
 
 // Device workspace of one single run: counters, its item descriptor and
@@ -187,7 +187,8 @@ int rt_group_slots(int M, int L);
 // true when a workgroup kernel with L threads exists for M channels
 bool rt_group_supported(int M, int L);
 size_t rt_group_lds_bytes(int N, int M, int L);
-int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, int64_t units, hipStream_t stream,
+int rt_subwave_auto_lanes(int M, int64_t units, int waves_per_cu);
+int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStream_t stream,
                       int* grid_used);
 // the workgroup mapping with the propensities in LDS (kernels_group_lds.hip):
 // the kernel for a class, or nullptr when its LDS does not fit; it reads the

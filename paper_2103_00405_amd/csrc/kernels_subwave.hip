@@ -112,6 +112,10 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
     extern __shared__ __align__(16) char dyn_lds[];
     __shared__ rt_log_lds<kBlock / 64> log_lds;
     const auto sc = log_lds.init();
+    __shared__ rt_wave_share wave_shares[kBlock / 64];
+    rt_wave_share& share = wave_shares[tid >> 6];
+    share.clear();
+    share.start_item(false);
     const int NP = (C.max_N + 3) & ~3;
     // this lane's slots: entry s 64 of each array
     double* const la = (double*)(dyn_lds + (tid >> 6) * wave_lds_bytes(L, S, NP)) + lane;
@@ -136,7 +140,7 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
     double t = 0.0, t_end = 0.0, s_next = 0.0;
     int32_t g = 0;
     unsigned long long hash = kFnvOffset;
-    bool active = lane / L < C.lanes, fresh = true, capped = false;
+    bool active = true, fresh = true, capped = false;
     uint32_t waiting = 0u;                                 // slots whose next draw is not made yet
     float g_min = 1e-30f;                                  // smallest gap the binary32 order takes
     // rate schedule: breakpoints passed, and the next one
@@ -298,14 +302,13 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
                     if (it->status) it->status[r] = (uint8_t)st;
                     if (it->seq_hash) it->seq_hash[r] = hash;
                     if (it->tie_step) it->tie_step[r] = tie;
-                    atomicAdd(&ws->firings, (unsigned long long)fired);
-                    atomicAdd(&ws->status_count[st], 1ull);
+                    share.finished(fired, st);
                 }
             }
             if (stop) {
                 // ---- take the next trajectory unit
                 unsigned long long u = 0;
-                if (li == 0) u = atomicAdd(&ws->next_unit, 1ull);
+                if (li == 0) u = (unsigned long long)share.take(&ws->next_unit, total);
                 u = __shfl(u, gbase, 64);
                 rt_wave_lds_fence();                          // X is reused
                 fresh = false;
@@ -456,6 +459,7 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
         hash = (hash ^ (unsigned long long)(uint32_t)mu) * kFnvPrime;
         capped = fired >= C.max_firings;
     }
+    share.flush(ws);
 }
 
 typedef void (*subwave_kernel_t)(rt_class_dev);
@@ -470,10 +474,10 @@ subwave_kernel_t select_subwave(int L, int S, bool sched)
 {
 #define RT_CASE(l, s) if (L == l && S == s) return sw_pick<l, s>(sched);
     RT_CASE(4, 2) RT_CASE(4, 4) RT_CASE(4, 6) RT_CASE(4, 8)
-    RT_CASE(8, 4) RT_CASE(8, 6) RT_CASE(8, 8)
-    RT_CASE(16, 4) RT_CASE(16, 6) RT_CASE(16, 8)
-    RT_CASE(32, 4) RT_CASE(32, 6) RT_CASE(32, 8)
-    RT_CASE(64, 4) RT_CASE(64, 6) RT_CASE(64, 8)
+    RT_CASE(8, 2) RT_CASE(8, 4) RT_CASE(8, 6) RT_CASE(8, 8)
+    RT_CASE(16, 2) RT_CASE(16, 4) RT_CASE(16, 6) RT_CASE(16, 8)
+    RT_CASE(32, 2) RT_CASE(32, 4) RT_CASE(32, 6) RT_CASE(32, 8)
+    RT_CASE(64, 2) RT_CASE(64, 4) RT_CASE(64, 6) RT_CASE(64, 8)
 #undef RT_CASE
     return nullptr;
 }
@@ -489,19 +493,34 @@ int rt_subwave_lanes(int M)
     return L;
 }
 
-// Slots per lane: the fewest of 2 (4 lanes only), 4, 6, 8 that hold M channels
-// (0: none).
+// Lanes per trajectory when nothing else says: as many as keep the units'
+// wavefronts within waves_per_cu, at least 8 and rt_subwave_lanes.  More lanes
+// are fewer slots and fewer groups a wavefront, so a faster firing, while a
+// wavefront has its SIMD to itself; on a full device fewer lanes do more per
+// instruction (45 channels, lanes 8 / 16 / 32 / 64: 300 trajectories 3.7 / 2.8
+// / 2.6 / 2.4 ms, 3000 3.8 / 2.9 / 3.4 / 3.7 ms, 30000 7.2 / 8.9 / 13.4 / 22.6
+// ms; 20 channels at 4 lanes: 2.6, 2.7 and 3.3 ms against 1.7, 1.7 and 2.7 at 8).
+int rt_subwave_auto_lanes(int M, int64_t units, int waves_per_cu)
+{
+    int L = std::max(8, rt_subwave_lanes(M));
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return L;
+    while (L < 64 && units * (2 * L) <= (int64_t)cus * waves_per_cu * 64) L <<= 1;
+    return L;
+}
+
+// Slots per lane: the fewest of 2, 4, 6, 8 that hold M channels (0: none).
 int rt_subwave_slots(int M, int L)
 {
     const int s = (M + L - 1) / L;
-    if (L == 4 && s <= 2) return 2;
-    return s <= 4 ? 4 : (s <= 6 ? 6 : (s <= 8 ? 8 : 0));
+    return s <= 2 ? 2 : s <= 4 ? 4 : (s <= 6 ? 6 : (s <= 8 ? 8 : 0));
 }
 
-int rt_launch_subwave(int max_M, const rt_class_dev& C_, int L, int grid, int64_t units,
-                      hipStream_t stream, int* grid_used)
+int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStream_t stream,
+                      int* grid_used)
 {
-    rt_class_dev C = C_;
     const int S = rt_subwave_slots(max_M, L);
     subwave_kernel_t kfn = select_subwave(L, S, C.has_schedule != 0);
     if (!kfn) return rt_fail(RTSSA_E_UNSUPPORTED, "no sub-wave kernel for this size");
@@ -515,7 +534,6 @@ int rt_launch_subwave(int max_M, const rt_class_dev& C_, int L, int grid, int64_
         hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)
         return rt_fail(RTSSA_E_HIP, "cannot raise the LDS limit");
-    C.lanes = 64 / L;
     if (grid <= 0) {
         int dev = 0, cus = 0, per_cu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||

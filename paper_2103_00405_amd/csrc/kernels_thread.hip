@@ -121,85 +121,6 @@ __device__ __forceinline__ void rt_two_smallest(const float (&v)[MT], float& g1,
     }
 }
 
-// One wavefront's share of the trajectory counter and of the run's counts, in
-// LDS.  Lanes take trajectories from the reserved range [next, end); when a
-// pass needs more than are left, one lane reserves as many as the stopping
-// lanes need, and more while many trajectories are left (a quarter of an even
-// share of the rest, at most 64).  Firings and end states are summed here and
-// added to the run's counters once, when the wavefront ends.  With one
-// device-wide atomic per trajectory for the trajectory and two for the counts,
-// all on one line, ensembles of short trajectories were bound by those: the
-// expectation and gradient of a birth-death process over 2^18 trajectories of
-// 200 firings took 5.73 ms, 2.25 ms this way.
-struct rt_wave_share {
-    int64_t next, end;
-    unsigned long long firings;
-    uint32_t status[4];
-
-    // A wavefront that runs its item alone (a batch) owns every trajectory.
-    __device__ __forceinline__ void start_item(bool own)
-    {
-        if ((threadIdx.x & 63u) == 0) {
-            next = 0;
-            end = own ? INT64_MAX : 0;
-        }
-        rt_wave_lds_fence();
-    }
-
-    // The next trajectory of each active lane (>= R: none left).
-    __device__ __forceinline__ int64_t take(unsigned long long* ctr, int64_t R)
-    {
-        const unsigned long long takers = __ballot(true);
-        const int want = __popcll(takers);
-        const int rank = __popcll(takers & ((1ull << (threadIdx.x & 63u)) - 1ull));
-        const int64_t n0 = next, e0 = end, left = e0 - n0;
-        int64_t r = n0 + rank;
-        rt_wave_lds_fence();
-        if (left < want) {                                 // the same in every lane
-            const float waves = (float)(gridDim.x * (blockDim.x >> 6));
-            const int share = (int)fminf((float)(R - e0) * 0.25f / waves, 64.0f);
-            const int n = max(want - (int)left, share);
-            unsigned long long at = 0;
-            if (rank == 0) at = atomicAdd(ctr, (unsigned long long)n);
-            at = rt_first_lane_u64(at);
-            if (rank >= left) r = (int64_t)at + (rank - left);
-            if (rank == 0) {
-                next = (int64_t)at + (want - left);
-                end = (int64_t)at + n;
-            }
-        } else if (rank == 0) {
-            next = n0 + want;
-        }
-        rt_wave_lds_fence();
-        return r;
-    }
-
-    __device__ __forceinline__ void clear()
-    {
-        if ((threadIdx.x & 63u) == 0) {
-            firings = 0ull;
-            for (int q = 0; q < 4; ++q) status[q] = 0u;
-        }
-        rt_wave_lds_fence();
-    }
-
-    __device__ __forceinline__ void finished(uint32_t fired, int st)
-    {
-        atomicAdd(&firings, (unsigned long long)fired);
-        atomicAdd(&status[st], 1u);
-    }
-
-    __device__ __forceinline__ void flush(rt_ws* ws)
-    {
-        rt_wave_lds_fence();
-        if ((threadIdx.x & 63u) == 0) {
-            if (firings) atomicAdd(&ws->firings, firings);
-            for (int q = 0; q < 4; ++q)
-                if (status[q]) atomicAdd(&ws->status_count[q], (unsigned long long)status[q]);
-        }
-    }
-};
-
 // Sample points kept in LDS per wavefront.
 constexpr int kGridLds = 128;
 
