@@ -6,15 +6,21 @@
 // thread k mod L, slot k / L (slots past M are frozen channels).  Per thread,
 // registers hold each slot's T_k, P_k, the channel's next unit-exponential
 // draw E(k, n_k + 1) (computed ahead, off the firing's critical path) and
-// n_k.  LDS holds (a_k, 1/a_k) of every
-// channel and two buffers of the species counts X.
+// n_k.  LDS holds a_k and a binary32 1/a_k of every channel and two buffers of
+// the species counts X.
 //
 // One firing (section 4, Table 2, in the internal-time form of Eq. 14-16):
-//   pass    every thread reads (a_k, 1/a_k) of its slots, forms the gaps
-//           (P_k - T_k)/a_k and a local argmin with second minimum;
-//   argmin  across the wavefront by DPP and permlane exchanges, across
-//           wavefronts through LDS -- the firing's only barrier; lowest k wins
-//           ties (Eq. 25);
+//   pass    every thread forms the gaps (P_k - T_k) / a_k of its slots in
+//           binary32, with the thread and slot in their low bits, and keeps its
+//           two smallest;
+//   argmin  one 32-bit minimum per lane exchange across the wavefront, across
+//           wavefronts through LDS -- the firing's only barrier; the winner's
+//           exact gap from one reciprocal; where a second gap is close, or the
+//           smallest is no plain positive number, the exact binary64 selection
+//           (lowest k wins ties, Eq. 25) behind a second barrier.  Against
+//           binary64 gaps, their second minimum and cached RN(1 / a_k):
+//           1000 species, 4000 channels, 512 trajectories 150.5 -> 124.5 ms
+//           (the firing's latency bounds it: 2 wavefronts a SIMD);
 //   event   every wavefront loads mu's fixed-stride rows (its jump v_mu and
 //           the records of the channels D(mu) reading a changed species --
 //           Gibson & Bruck's dependency graph, cited in section 5 -- with
@@ -45,8 +51,18 @@
 
 namespace {
 
+// A wavefront's candidate: its smallest selection key, whether another of its
+// keys is within reach of it, and that channel's P - T and a (which the
+// wavefront that owns the channel may rewrite as soon as it has passed the
+// firing's barrier, so no other may read it from LDS after that).
+struct g2_part {
+    int32_t key, close;
+    double df, a;
+};
+
 struct g2_shared {
-    rt_sel_part part[2][16];             // per selection parity, per wavefront
+    g2_part part[2][16];                 // per firing parity, per wavefront
+    rt_sel_part exact[2][16];            // the same for the exact selection
     unsigned long long next_traj;
     uint32_t log_scratch[16][RT_LOG_SCRATCH];
 };
@@ -70,12 +86,21 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
     const rt_cptr<int64_t> unit_start = rt_const(C.unit_start);
     const int64_t total = unit_start[C.count];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // a_k and 1/a_k as two arrays, so that a wavefront reading either for its
-    // slots touches consecutive 8-byte words (no bank conflicts)
+    // a_k and a binary32 1/a_k as two arrays, so that a wavefront reading either
+    // for its slots touches consecutive words (no bank conflicts)
     double* const pa = g2_lds;                                    // [L S] a_k
-    double* const pinv = g2_lds + L * S;                          // [L S] 1/a_k
+    float* const pinv = (float*)(g2_lds + L * S);                 // [L S] 1/a_k
     const int Npad = (C.max_N + 3) & ~3;
-    int32_t* const Xb = (int32_t*)(g2_lds + 2 * L * S);           // [2][Npad]
+    int32_t* const Xb = (int32_t*)(pinv + L * S);                 // [2][Npad]
+    // a selection key: a binary32 gap with the thread and the slot in its low bits
+    constexpr int kSlotBits = S <= 1 ? 0 : 32 - __builtin_clz((unsigned)(S - 1));
+    constexpr int kKeyBits = LOG2L + kSlotBits;
+    constexpr int32_t kKey = (1 << kKeyBits) - 1;
+    // two gaps of different order differ by more than what the keys drop
+    constexpr float kApart = 1.0f + 1.0f / (float)(1 << (21 - kKeyBits));
+    auto reach = [](int32_t key) {
+        return __float_as_int(__int_as_float(key & ~kKey) * kApart) | kKey;
+    };
     const rt_log_ctx<rt_log_const_tab> sc{{}, sh.log_scratch[wave]};
 
     double T[S], P[S], En[S];
@@ -123,15 +148,17 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
             Xb[Npad + j] = v;
         }
         __syncthreads();
+        bool plain = true;
 #pragma unroll 1
         for (int s1 = 0; s1 < S; ++s1) {
             const int k = tid + s1 * L;
             const bool live = k < M;
-            double an = 0.0, in = __builtin_inf();
+            double an = 0.0;
             uint64_t m0 = 0x1FFFFFFFFFFFFFull, m1 = 0x1FFFFFFFFFFFFFull;   // u = 1: no work
             if (live) {
-                an = rt_propensity_mem(react[k], crate[k], Xb);
-                in = 1.0 / an;
+                const double c = crate[k];
+                an = rt_propensity_mem(react[k], c, Xb);
+                plain = plain && rt_plain_rate(c);
                 const rt_u4 w =
                     rt_philox4x32_10<false>(rt_u4{0u, (uint32_t)k, traj, net_id}, key0, key1);
                 m0 = (((uint64_t)w.y << 32) | w.x) >> 11;
@@ -142,7 +169,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
             const double p1 = rt_neglog_wave(m1, false, &ws->slow_logs, sc);
             const double p0 = live ? e0 : __builtin_inf();
             pa[k] = an;
-            pinv[k] = in;
+            pinv[k] = __builtin_amdgcn_rcpf((float)an);
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 P[s] = s == s1 ? p0 : P[s];
@@ -158,54 +185,98 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
         uint32_t fired = 0, tie = kTieNone;
         unsigned long long hash = kFnvOffset;
         int st = RTSSA_TRAJ_OK;
-        uint32_t reduces = 0;        // parity picks the argmin's LDS buffer
+        uint32_t reduces = 0;        // parity picks the selection's LDS buffer
+        // the smallest gap the binary32 order takes
+        float g_min = __syncthreads_or(!plain) ? __builtin_inff() : 1e-30f;
 
         for (;;) {
-            // ---- pass: gaps (P_k - T_k) / a_k and the lane's two smallest.
-            // A frozen channel (a_k = 0, 1/a_k = +inf) gives +inf while
-            // P_k > T_k; a negative raw gap (clamped to 0) or a frozen channel
-            // with P_k <= T_k (NaN, -inf) is rare and sends the wavefront
-            // through the exact form below.
-            double d1 = __builtin_inf(), d2 = __builtin_inf();
-            int ks = 0;
-            bool bad = false;
-            // every slot's 1/a_k read at once (the scheduling barrier keeps the
-            // compiler from interleaving the reads with the arithmetic and
-            // waiting on each in turn)
-            double iv[S];
+            // ---- pass: the gaps (P_k - T_k) / a_k in binary32 as keys, the
+            // lane's two smallest.  Every slot's 1/a_k is read at once (the
+            // scheduling barrier keeps the compiler from interleaving the reads
+            // with the arithmetic and waiting on each in turn).
+            float iv[S];
 #pragma unroll
             for (int s = 0; s < S; ++s) iv[s] = pinv[tid + s * L];
             __builtin_amdgcn_sched_barrier(0);
+            int32_t k1 = 0x7FFFFFFF, k2 = 0x7FFFFFFF;
 #pragma unroll
             for (int s = 0; s < S; ++s) {
-                const double raw = (P[s] - T[s]) * iv[s];
-                bad = bad || !(raw >= 0.0);
-                const bool lt = raw < d1;          // the lower slot wins equal values
-                d2 = fmin(d2, fmax(d1, raw));
-                d1 = fmin(d1, raw);
-                ks = lt ? s : ks;
+                const float gap = (float)(P[s] - T[s]) * iv[s];
+                const int32_t key =
+                    (int32_t)rt_and_or(__float_as_uint(gap), (uint32_t)~kKey, (uint32_t)s);
+                k2 = rt_med3_i32(k1, k2, key);
+                k1 = min(k1, key);
             }
-            if (__builtin_expect(__ballot(bad) != 0ull, 0)) {
-                d1 = __builtin_inf();
-                d2 = __builtin_inf();
-                ks = 0;
+            k1 |= tid << kSlotBits;
+            // ---- selection over the workgroup: the firing's barrier.  Each
+            // wavefront brings its smallest key, that channel's P - T and whether
+            // another of its keys is within reach; the workgroup's smallest
+            // decides unless a second is within its reach or it is no plain
+            // positive number (every thread sees the same parts).
+            const int32_t kw = rt_group_min_i32<64>(k1);
+            const int sw = __builtin_amdgcn_readfirstlane(kw & ((1 << kSlotBits) - 1));
+            double dw = 0.0;
+            if constexpr (SCHED) {
 #pragma unroll
-                for (int s = 0; s < S; ++s) {
-                    const double raw = (P[s] - T[s]) * pinv[tid + s * L];
-                    const double d = pa[tid + s * L] == 0.0 ? __builtin_inf() : fmax(raw, 0.0);
-                    const bool lt = d < d1;
-                    d2 = fmin(d2, fmax(d1, d));
-                    d1 = fmin(d1, d);
-                    ks = lt ? s : ks;
-                }
+                for (int s = 0; s < S; ++s) dw = s == sw ? P[s] - T[s] : dw;
+            } else {
+                dw = P[sw] - T[sw];
             }
-            // ---- selection over the workgroup: the firing's barrier
-            const rt_min2 sel = rt_select_group<L>(d1, d2, tid + (ks << LOG2L),
-                                                   sh.part[reduces & 1u]);
+            const bool close = __ballot((k1 == kw ? k2 : k1) <= reach(kw)) != 0ull;
+            g2_part* const parts = sh.part[reduces & 1u];
+            if (k1 == kw) parts[wave] = g2_part{kw, close ? 1 : 0, dw, pa[tid + sw * L]};
+            __syncthreads();
+            g2_part best = parts[0];
+            bool amb = false;
+            if constexpr (W > 1) {
+                g2_part pt[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) pt[w] = parts[w];
+                int32_t second = 0x7FFFFFFF;
+#pragma unroll
+                for (int w = 1; w < W; ++w) {
+                    const bool lt = pt[w].key < best.key;
+                    second = min(second, lt ? best.key : pt[w].key);
+                    best.key = lt ? pt[w].key : best.key;
+                    best.close = lt ? pt[w].close : best.close;
+                    best.df = lt ? pt[w].df : best.df;
+                    best.a = lt ? pt[w].a : best.a;
+                }
+                amb = second <= reach(best.key);
+            }
+            amb = amb || best.close != 0 || !(__int_as_float(best.key & ~kKey) > g_min);
+            const int kb = __builtin_amdgcn_readfirstlane(best.key);
+            int mu = ((kb & ((1 << kSlotBits) - 1)) << LOG2L) + ((kb & kKey) >> kSlotBits);
+            double d1 = best.df * rt_recip(best.a);
+            bool near = false, clamped = false;
+            if (__builtin_expect(__builtin_amdgcn_readfirstlane(amb ? 1 : 0), 0)) {
+                // exact gaps max(0, RN((P - T) RN(1 / a))), +inf for a frozen
+                // channel, and the exact selection with second minimum
+                double e1 = __builtin_inf(), e2 = __builtin_inf();
+                int ks = 0;
+#pragma unroll 1
+                for (int s = 0; s < S; ++s) {
+                    double df = 0.0;
+#pragma unroll
+                    for (int q = 0; q < S; ++q) df = q == s ? P[q] - T[q] : df;
+                    const double a = pa[tid + s * L];
+                    const double raw = df * (1.0 / a);
+                    const double e = a == 0.0 ? __builtin_inf() : fmax(raw, 0.0);
+                    const bool lt = e < e1;
+                    e2 = fmin(e2, fmax(e1, e));
+                    e1 = fmin(e1, e);
+                    ks = lt ? s : ks;
+                    clamped = lt ? raw < 0.0 : clamped;
+                }
+                const rt_min2 sel = rt_select_group<L>(e1, e2, tid + (ks << LOG2L),
+                                                       sh.exact[reduces & 1u]);
+                d1 = sel.d1;
+                mu = __builtin_amdgcn_readfirstlane(sel.k);
+                near = rt_near_tie(sel.d1, sel.d2);
+                // (a zero gap clamped from a negative raw gap)
+                clamped = clamped && d1 == 0.0 && tid == (mu & (L - 1));
+            }
             ++reduces;
-            d1 = sel.d1;
-            d2 = sel.d2;
-            const int mu = __builtin_amdgcn_readfirstlane(sel.k);
             const double t_new = t + d1;
             const int32_t* const Xc = Xb + (fired & 1u) * Npad;      // X after `fired` firings
             int32_t* const Xn = Xb + ((fired + 1u) & 1u) * Npad;     // the other buffer
@@ -237,15 +308,19 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                 crate = rt_const(net.sched_c) + (size_t)piece * M;
                 ++piece;
                 b_next = piece < sB ? rt_const(net.sched_t)[piece] : __builtin_inf();
+                bool ok_rates = true;
 #pragma unroll 1
                 for (int s1 = 0; s1 < S; ++s1) {
                     const int k = tid + s1 * L;
                     if (k < M) {
-                        const double an = rt_propensity_mem(react[k], crate[k], Xc);
+                        const double c = crate[k];
+                        const double an = rt_propensity_mem(react[k], c, Xc);
                         pa[k] = an;
-                        pinv[k] = 1.0 / an;
+                        pinv[k] = __builtin_amdgcn_rcpf((float)an);
+                        ok_rates = ok_rates && rt_plain_rate(c);
                     }
                 }
+                g_min = __syncthreads_or(!ok_rates) ? __builtin_inff() : 1e-30f;
                 continue;
             }
             if (d1 == __builtin_inf()) { st = RTSSA_TRAJ_ABSORBED; break; }
@@ -279,7 +354,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
             const int2 rr = make_int2(gr.y, gr.z);
             // (with a rate schedule the rates in force come from the piece)
             const double cr = SCHED ? crate[mine ? kd : mu] : gc;
-            if (rt_near_tie(d1, d2)) {
+            if (near) {
                 if (tid == 0) atomicAdd(&ws->near_ties, 1ull);
                 tie = tie == kTieNone ? fired : tie;
             }
@@ -300,13 +375,6 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
             if (__ballot(!okl) != 0ull) { st = RTSSA_TRAJ_OVERFLOW; break; }
             // ---- internal clocks (Eq. 15), the fired channel's firing time and
             // next draw (Eq. 26)
-            bool clamped = false;
-            if (d1 == 0.0 && tid == owner) {
-                // a zero gap: was it clamped from a negative raw gap?
-#pragma unroll
-                for (int s = 0; s < S; ++s)
-                    if (s == sm) clamped = (P[s] - T[s]) * pinv[mu] < 0.0;
-            }
             // (a_k as read by the pass: this wavefront writes its channels'
             // entries only below)
             {
@@ -369,7 +437,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                     if (kind == RT_H_TWO) v1 = Xc[s1] + dd.y;
                     const double an = rt_propensity_counts(kind, (uint32_t)v0, (uint32_t)v1, cr);
                     pa[kd] = an;
-                    pinv[kd] = 1.0 / an;
+                    pinv[kd] = __builtin_amdgcn_rcpf((float)an);
                 }
                 if (n_other > 63) {
                     // the rest of D(mu) from its 64th other channel on
@@ -383,7 +451,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                                                             r2.x & RT_SPECIES_MASK, r2.y,
                                                             crate[k2], xnew);
                             pa[k2] = an;
-                            pinv[k2] = 1.0 / an;
+                            pinv[k2] = __builtin_amdgcn_rcpf((float)an);
                         }
                     }
                 }
@@ -454,7 +522,7 @@ g2_kernel_t select_g2(int L, int S, bool sched)
 
 size_t rt_group_lds2_bytes(int N, int L, int S)
 {
-    return (size_t)L * S * 16 + (size_t)2 * ((N + 3) & ~3) * 4;
+    return (size_t)L * S * 12 + (size_t)2 * ((N + 3) & ~3) * 4;
 }
 
 // The LDS-propensity kernel for this class, or nullptr when it does not

@@ -56,38 +56,6 @@ constexpr int kDrawLanes = 16;
 // and 2 at 8).
 constexpr int subwave_min_waves(int S, bool SCHED) { return S <= 4 ? 4 : 3; }
 
-__device__ __forceinline__ int32_t med3_i32(int32_t a, int32_t b, int32_t c)
-{
-    int32_t r;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-// Smallest value over aligned groups of W lanes, in every lane.
-template <int W>
-__device__ __forceinline__ int32_t group_min_i32(int32_t v)
-{
-    if (W >= 2) v = min(v, rt_dpp<0xB1>(v));       // quad_perm [1,0,3,2]
-    if (W >= 4) v = min(v, rt_dpp<0x4E>(v));       // quad_perm [2,3,0,1]
-    if (W >= 8) v = min(v, rt_dpp<0x141>(v));      // row_half_mirror
-    if (W >= 16) v = min(v, rt_dpp<0x140>(v));     // row_mirror
-    uint32_t p, q;
-    if (W >= 32) {
-        rt_swap<16>((uint32_t)v, p, q);
-        v = min((int32_t)p, (int32_t)q);
-    }
-    if (W >= 64) {
-        rt_swap<32>((uint32_t)v, p, q);
-        v = min((int32_t)p, (int32_t)q);
-    }
-    return v;
-}
-
-__device__ __forceinline__ bool plain_rate(double c)
-{
-    return c == 0.0 || (c >= 0x1p-100 && c <= 0x1p60);
-}
-
 // LDS bytes of one wavefront: per slot and lane a_k, the next draw, 1 / a_k
 // and n_k; then X of each group.
 constexpr size_t wave_lds_bytes(int L, int S, int NP)
@@ -162,10 +130,10 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
             const float gap = (float)df[s] * linv[s * 64];
             const int32_t key = (int32_t)rt_and_or(__float_as_uint(gap), (uint32_t)~kKey,
                                                    (uint32_t)(s * L + li));
-            k2 = med3_i32(k1, k2, key);
+            k2 = rt_med3_i32(k1, k2, key);
             k1 = min(k1, key);
         }
-        const int32_t kbest = group_min_i32<L>(k1);
+        const int32_t kbest = rt_group_min_i32<L>(k1);
         int mu = kbest & kKey;
         // rare: the second smallest is close (a lane's candidate: its smallest,
         // or its second where it owns mu), or the smallest is no plain number
@@ -353,7 +321,7 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
                                                          &ws->slow_logs, sc);
                             const double c = rt_const(it->net.c)[k];
                             an = rt_propensity_mem(rt_const(it->net.react)[k], c, X);
-                            plain = plain && plain_rate(c);
+                            plain = plain && rt_plain_rate(c);
                         }
                         la[s1 * 64] = an;
                         linv[s1 * 64] = __builtin_amdgcn_rcpf((float)an);
@@ -386,7 +354,7 @@ __global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwav
                         const double an = rt_propensity_mem(rt_const(net->react)[k], cr[k], X);
                         la[s * 64] = an;
                         linv[s * 64] = __builtin_amdgcn_rcpf((float)an);
-                        plain = plain && plain_rate(cr[k]);
+                        plain = plain && rt_plain_rate(cr[k]);
                     }
                 }
                 g_min = (__ballot(!plain) & gmask) ? __builtin_inff() : 1e-30f;

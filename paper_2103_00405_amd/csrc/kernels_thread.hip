@@ -238,13 +238,9 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
 #pragma unroll
             for (int j = 0; j < NT; ++j) up = max(up, nu[k][j]);
         const uint32_t x_safe = 0x7FFFFFFFu - (uint32_t)up;
-        // rates for which every a_k > 0 and every gap is a normal binary32 number
-        // or overflows towards the exact form: 0 or 2^-100 .. 2^60 (h < 2^62, and
-        // 1e-32 < P - T < 37); other items take the exact form at every firing
-        auto plain_rate = [](double v) { return v == 0.0 || (v >= 0x1p-100 && v <= 0x1p60); };
         bool plain = true;
 #pragma unroll
-        for (int k = 0; k < MT; ++k) plain = plain && plain_rate(c[k]);
+        for (int k = 0; k < MT; ++k) plain = plain && rt_plain_rate(c[k]);
 
         // ---- trajectory state
         int32_t X[NT];
@@ -486,7 +482,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                     t_stop = fmin(s_next, fmin(b_next, t_end));
                     bool ok_rates = true;
 #pragma unroll
-                    for (int k = 0; k < MT; ++k) ok_rates = ok_rates && plain_rate(cl[k]);
+                    for (int k = 0; k < MT; ++k) ok_rates = ok_rates && rt_plain_rate(cl[k]);
                     g_min = ok_rates ? 1e-30f : __builtin_inff();
                     refresh();
                 }

@@ -99,6 +99,15 @@ __device__ __forceinline__ double rt_recip(double a)
     return fma(fma(-a, y, 1.0), y, y);
 }
 
+// Rates for which every a_k > 0 is a normal binary32 number or overflows, and
+// every gap too (h < 2^62, and 1e-32 < P - T < 37): 0 or 2^-100 .. 2^60.  The
+// kernels that order gaps in binary32 take the exact form at every firing when
+// some rate is outside.
+__device__ __forceinline__ bool rt_plain_rate(double c)
+{
+    return c == 0.0 || (c >= 0x1p-100 && c <= 0x1p60);
+}
+
 // A firing channel's internal times: T = P, then P += E.  In place (the
 // compiler adds into a temporary and copies) and never as selects.
 __device__ __forceinline__ void rt_land(double& T, double& P, double E)

@@ -257,3 +257,31 @@ __device__ __forceinline__ rt_min2 rt_select_group(double d1, double d2, int32_t
         return rt_min2{q[0].d1, q[0].d2, q[0].k};
     }
 }
+
+// Median of three.
+__device__ __forceinline__ int32_t rt_med3_i32(int32_t a, int32_t b, int32_t c)
+{
+    int32_t r;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// Smallest value over aligned groups of W lanes, in every lane.
+template <int W>
+__device__ __forceinline__ int32_t rt_group_min_i32(int32_t v)
+{
+    if (W >= 2) v = min(v, rt_dpp<0xB1>(v));       // quad_perm [1,0,3,2]
+    if (W >= 4) v = min(v, rt_dpp<0x4E>(v));       // quad_perm [2,3,0,1]
+    if (W >= 8) v = min(v, rt_dpp<0x141>(v));      // row_half_mirror
+    if (W >= 16) v = min(v, rt_dpp<0x140>(v));     // row_mirror
+    uint32_t p, q;
+    if (W >= 32) {
+        rt_swap<16>((uint32_t)v, p, q);
+        v = min((int32_t)p, (int32_t)q);
+    }
+    if (W >= 64) {
+        rt_swap<32>((uint32_t)v, p, q);
+        v = min((int32_t)p, (int32_t)q);
+    }
+    return v;
+}

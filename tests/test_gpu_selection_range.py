@@ -1,6 +1,6 @@
 """Selection in binary32 keys against the oracle over the rates' whole range.
 
-The thread and sub-wave kernels order the gaps (P - T) / a in binary32 and fall
+The thread, sub-wave and workgroup kernels order the gaps (P - T) / a in binary32 and fall
 back to the exact selection where that order cannot decide.  Scaling every rate
 by f and the times by 1 / f moves gaps and propensities through binary32's
 normal range, past it and into its subnormals; every output stays bit-exact.
@@ -42,18 +42,23 @@ def _net(M, seed):
     return spec, x0, 150.0 / a0
 
 
-@pytest.mark.parametrize("M,lanes", [(5, 0), (40, 8), (100, 16), (300, 64)])
+def _mapping(lanes):
+    """block and mapping of a lane count: 0 automatic, <= 64 sub-wave, else workgroup."""
+    return dict(block=lanes, **({"mapping": 2 if lanes <= 64 else 3} if lanes else {}))
+
+
+@pytest.mark.parametrize("M,lanes", [(5, 0), (40, 8), (100, 16), (300, 64), (700, 128),
+                                     (1100, 256)])
 @pytest.mark.parametrize("f", [1e-200, 1e-45, 1e-33, 1e-20, 1e17, 1e40, 1e200])
 def test_scaled_rates_bit_exact(M, lanes, f):
     spec, x0, t_end = _net(M, 100 + M)
     spec = W.with_rates(spec, np.asarray(spec.c) * f)
     t_end = t_end / f
-    ref = _compare(spec, x0, t_end, np.linspace(0.0, t_end, 9), 70, 3, block=lanes,
-                   **({"mapping": 2} if lanes else {}))
+    ref = _compare(spec, x0, t_end, np.linspace(0.0, t_end, 9), 70, 3, **_mapping(lanes))
     assert ref["stats"]["firings"] > 70 * 30
 
 
-@pytest.mark.parametrize("M,lanes", [(6, 0), (48, 8), (200, 32)])
+@pytest.mark.parametrize("M,lanes", [(6, 0), (48, 8), (200, 32), (600, 128)])
 def test_channels_far_apart_bit_exact(M, lanes):
     """A third of the channels at 1e-60 and 1e-45 of the others' rates: they hold
     the binary32 form at +inf without being frozen."""
@@ -61,8 +66,8 @@ def test_channels_far_apart_bit_exact(M, lanes):
     c = np.asarray(spec.c).copy()
     c[::3] *= 1e-60
     c[1::6] *= 1e-45
-    _compare(W.with_rates(spec, c), x0, t_end, np.linspace(0.0, t_end, 5), 64, 4, block=lanes,
-             **({"mapping": 2} if lanes else {}))
+    _compare(W.with_rates(spec, c), x0, t_end, np.linspace(0.0, t_end, 5), 64, 4,
+             **_mapping(lanes))
 
 
 @pytest.mark.parametrize("lanes", [4, 8, 64])
