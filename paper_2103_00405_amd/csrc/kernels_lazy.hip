@@ -65,9 +65,9 @@ struct rt_lazy_rec {                     // a channel's state in the workspace
 // t + max(0, RN(RN(P - T) * RN(1 / a))); *clamped when the raw gap is negative.
 __device__ __forceinline__ double lazy_tau(double t, double T, double P, double a, bool* clamped)
 {
-    const double raw = (P - T) * (1.0 / a);
+    const double raw = (P - T) * rt_recip(a);
     *clamped = a != 0.0 && raw < 0.0;
-    return a == 0.0 ? __builtin_inf() : t + fmax(raw, 0.0);
+    return a == 0.0 ? __builtin_inf() : t + (raw < 0.0 ? 0.0 : raw);
 }
 
 // The tree of one trajectory: level 0 holds the leaves (tau; channel =
@@ -137,64 +137,75 @@ __device__ __forceinline__ void lazy_store(const lazy_tree& tr, int l, int j, co
     tr.kk[l][j] = v.k;
 }
 
-// The smallest entry (and its channel) over the wavefront, in every lane: the
-// smallest value by a min reduction, then the channel of the one lane holding
-// it; when several lanes hold it (or every value is +inf) the lowest of their
-// channels (the order of lanes is not channel order).
-__device__ __forceinline__ lazy_min lazy_wave_argmin(const lazy_min& v)
-{
-    const double m = rt_wave_min_f64(v.d);
-    unsigned long long own = __ballot(v.d == m);
-    int32_t k;
-    if (__builtin_expect(__popcll(own) == 1, 1)) {
-        k = __builtin_amdgcn_readlane(v.k, __ffsll((long long)own) - 1);
-    } else {
-        k = 0x7FFFFFFF;
-        while (own) {
-            k = min(k, (int32_t)__builtin_amdgcn_readlane(v.k, __ffsll((long long)own) - 1));
-            own &= own - 1ull;
-        }
-    }
-    return lazy_min{m, k};
-}
-
-// The top level (at most kTopMax entries; lane l holds entries l + 64 i) as
-// the lane's smallest entry (channel order wins ties: a lane's entries come in
-// channel order), the lane's second smallest and the index of its smallest;
-// the wavefront argmin of the lanes' smallest is the next event.
+// The top level (at most kTopMax entries; lane l holds entries l + 64 i, +inf
+// past the level's end): read at once, kept for the near-tie test.
+// TOP: the 64-entry chunks the kernel is built for, 2, 4 or 8 (skipping chunks by
+// scalar branches instead: 160 ms against 144 on the 4000-channel network).
+template <int TOP>
 struct lazy_top {
-    lazy_min m;
-    double d2;
-    int e1;
+    double v[TOP];
 };
 
-__device__ __forceinline__ lazy_top lazy_top_scan(const double* top_d, const int32_t* top_k,
-                                                  int top_cnt, bool leaves_on_top, int lane)
+template <int TOP>
+__device__ __forceinline__ lazy_top<TOP> lazy_top_read(const double* top_d, int top_cnt, int lane)
 {
-    double dv[kTopPer];
-    int32_t kv[kTopPer];
+    lazy_top<TOP> r;
 #pragma unroll
-    for (int i = 0; i < kTopPer; ++i) {
+    for (int i = 0; i < TOP; ++i) {
         const int e = lane + 64 * i;
-        dv[i] = __builtin_inf();
-        kv[i] = 0x7FFFFFFF;
-        if (64 * i < top_cnt && e < top_cnt) {           // the first test: every lane alike
-            dv[i] = top_d[e];
-            kv[i] = leaves_on_top ? e : top_k[e];
-        }
-    }
-    lazy_top r{lazy_min{__builtin_inf(), 0x7FFFFFFF}, __builtin_inf(), -1};
-    // chunks past the level's entries (the same in every lane) are skipped
-#pragma unroll
-    for (int i = 0; i < kTopPer; ++i) {
-        if (64 * i >= top_cnt) break;
-        const bool lt = dv[i] < r.m.d;
-        r.d2 = rt_min_sel(r.d2, lt ? r.m.d : dv[i]);
-        r.m.d = lt ? dv[i] : r.m.d;
-        r.m.k = lt ? kv[i] : r.m.k;
-        r.e1 = lt ? lane + 64 * i : r.e1;
+        r.v[i] = __builtin_inf();
+        if (64 * i < top_cnt && e < top_cnt) r.v[i] = top_d[e];   // the first test: every lane alike
     }
     return r;
+}
+
+// min of two times (no NaN, no -0) in one instruction.
+__device__ __forceinline__ double lazy_min2(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// The smallest entry of the top level and its channel, in every lane: the value
+// by minima over the lane's entries and a reduction over the wavefront, then the
+// entry by compares with it; several entries holding it (or every entry +inf)
+// give the lowest channel.  This ends the firing's serial chain; with the lane's
+// second smallest, index and channel carried through the scan it was 230 cycles
+// longer (1000 species, 4000 channels, 512 trajectories: 156 -> 144 ms).
+template <int TOP>
+__device__ __forceinline__ lazy_min lazy_next(const lazy_top<TOP>& tp, const int32_t* top_k,
+                                              bool leaves_on_top, int lane)
+{
+    double m = tp.v[0];
+#pragma unroll
+    for (int i = 1; i < TOP; ++i) m = lazy_min2(m, tp.v[i]);
+    m = lazy_min2(m, rt_dpp_f64<0xB1>(m));              // quad_perm [1,0,3,2]
+    m = lazy_min2(m, rt_dpp_f64<0x4E>(m));              // quad_perm [2,3,0,1]
+    m = lazy_min2(m, rt_dpp_f64<0x141>(m));             // row_half_mirror
+    m = lazy_min2(m, rt_dpp_f64<0x140>(m));             // row_mirror
+    double q;
+    double p = rt_swap_f64<16>(m, q);
+    m = lazy_min2(p, q);
+    p = rt_swap_f64<32>(m, q);
+    m = lazy_min2(p, q);
+    int at = -1;
+#pragma unroll
+    for (int i = TOP - 1; i >= 0; --i) at = tp.v[i] == m ? i : at;
+    unsigned long long own = __ballot(at >= 0);
+    const int e = lane + 64 * max(at, 0);
+    if (__builtin_expect(__popcll(own) == 1, 1)) {
+        const int eo = __builtin_amdgcn_readlane(e, __ffsll((long long)own) - 1);
+        return lazy_min{m, leaves_on_top ? eo : top_k[eo]};
+    }
+    int32_t k = 0x7FFFFFFF;
+    if (m != __builtin_inf() && at >= 0) k = leaves_on_top ? e : top_k[e];
+    while (own) {
+        const int32_t ko = __builtin_amdgcn_readlane(k, __ffsll((long long)own) - 1);
+        k = min(k, ko);
+        own &= own - 1ull;
+    }
+    return lazy_min{m, __builtin_amdgcn_readfirstlane(k)};
 }
 
 // The near-tie test of a firing (d1 = tau_mu - t).  The second smallest tau
@@ -207,9 +218,10 @@ __device__ __forceinline__ lazy_top lazy_top_scan(const double* top_d, const int
 // sibling i at level l < top (level_off holds each level's tau array as a
 // byte offset into the LDS region, a table in LDS so that the per-lane level
 // index does not turn into a private-memory array); every lane also takes its
-// own top-level minimum, or its second when it holds mu's ancestor.
+// own top-level entries but mu's ancestor.
+template <int TOP>
 __device__ __forceinline__ bool lazy_near_tie(const char* region, const uint32_t* level_off,
-                                              int top, int mu, const lazy_top& tp, int lane,
+                                              int top, int mu, const lazy_top<TOP>& tp, int lane,
                                               double t, double d1)
 {
     double sib = __builtin_inf();
@@ -220,8 +232,10 @@ __device__ __forceinline__ bool lazy_near_tie(const char* region, const uint32_t
         sib = (lane >> kFanLog) < top && i != (jl & (kFan - 1)) ? x : __builtin_inf();
     }
     const int anc = mu >> (kFanLog * top);
-    const double own = lane == (anc & 63) && tp.e1 == anc ? tp.d2 : tp.m.d;
-    return __ballot(rt_near_tie(d1, rt_min_sel(sib, own) - t)) != 0ull;
+#pragma unroll
+    for (int i = 0; i < TOP; ++i)
+        sib = lane + 64 * i == anc ? sib : rt_min_sel(sib, tp.v[i]);
+    return __ballot(rt_near_tie(d1, sib - t)) != 0ull;
 }
 
 // A touched channel's update (mu: fresh = true, T_mu = P_mu, P_mu += E;
@@ -249,8 +263,10 @@ __device__ __forceinline__ rt_lazy_rec lazy_touch(rt_lazy_rec rc, bool fresh, do
 // next event lies past the next breakpoint b (b < t_end), every channel runs
 // its clock to b at its old propensity, takes the next piece's rates and a new
 // next firing time from b, the tree is rebuilt, and nothing fires at b.
-template <bool SCHED>
-__global__ __launch_bounds__(64) void rt_lazy_kernel(rt_class_dev C, rt_lazy_rec* rec_ws,
+// (Without a schedule at most 128 VGPRs: in a batch three lazy wavefronts a SIMD
+// then leave room for one of another class.)
+template <bool SCHED, int TOP>
+__global__ __launch_bounds__(64, SCHED ? 1 : 4) void rt_lazy_kernel(rt_class_dev C, rt_lazy_rec* rec_ws,
                                                      unsigned long long* w_ws, uint32_t* n_ws,
                                                      int64_t m_stride)
 {
@@ -368,8 +384,8 @@ __global__ __launch_bounds__(64) void rt_lazy_kernel(rt_class_dev C, rt_lazy_rec
 
         // the next event: the top level's argmin, kept in registers (every
         // lane holds it) and recomputed at the end of each tree update
-        lazy_top top_e = lazy_top_scan(top_d, top_k, top_cnt, top == 0, lane);
-        lazy_min root = lazy_wave_argmin(top_e.m);
+        lazy_top<TOP> top_e = lazy_top_read<TOP>(top_d, top_cnt, lane);
+        lazy_min root = lazy_next<TOP>(top_e, top_k, top == 0, lane);
         double root_tau = root.d;
         int root_ch = root.k;
         double t = 0.0, s_next = it->G > 0 ? rt_const(it->s)[0] : __builtin_inf();
@@ -411,8 +427,8 @@ __global__ __launch_bounds__(64) void rt_lazy_kernel(rt_class_dev C, rt_lazy_rec
                         lazy_store(tr, l, j, lazy_node(tr, l, j));
                     rt_wave_lds_fence();
                 }
-                top_e = lazy_top_scan(top_d, top_k, top_cnt, top == 0, lane);
-                root = lazy_wave_argmin(top_e.m);
+                top_e = lazy_top_read<TOP>(top_d, top_cnt, lane);
+                root = lazy_next<TOP>(top_e, top_k, top == 0, lane);
                 root_tau = root.d;
                 root_ch = root.k;
                 continue;
@@ -510,8 +526,8 @@ __global__ __launch_bounds__(64) void rt_lazy_kernel(rt_class_dev C, rt_lazy_rec
                     }
                 }
             }
-            top_e = lazy_top_scan(top_d, top_k, top_cnt, top == 0, lane);
-            root = lazy_wave_argmin(top_e.m);
+            top_e = lazy_top_read<TOP>(top_d, top_cnt, lane);
+            root = lazy_next<TOP>(top_e, top_k, top == 0, lane);
             root_tau = root.d;
             root_ch = root.k;
             if (lane == 0) nks[mu] = nm + 1u;
@@ -565,8 +581,7 @@ __global__ __launch_bounds__(64) void rt_lazy_kernel(rt_class_dev C, rt_lazy_rec
 // r <= v_i (the last positive child if r passes them all) and subtracting the
 // children it passes; then mu's jump, the new propensities of mu and D(mu),
 // and their ancestors' sums.  A firing's draws do not depend on the state, so
-// the next firing's block and logarithm are computed while this firing's
-// loads are in flight.
+// 64 firings' blocks and logarithms are made at once, one firing a lane.
 
 static_assert(kFan == 8, "the sum tree adds 8 children pairwise");
 
@@ -577,15 +592,29 @@ __device__ __forceinline__ double dt_sum_node(const lazy_tree& tr, int l, int j)
     return ((a.x + a.y) + (b.x + b.y)) + ((c.x + c.y) + (d.x + d.y));
 }
 
-// E = RN(-ln u1) and the search's 53 bits of firing `fired`, every lane alike.
-__device__ __forceinline__ double dt_draw(uint32_t key0, uint32_t key1, uint32_t traj,
-                                          uint32_t net_id, uint32_t fired, uint64_t* m2,
-                                          unsigned long long* slow, uint32_t* sc)
+// The numbers of 64 consecutive firings, one firing a lane: E = RN(-ln u1) and
+// u2 = (m + 1) 2^-53 of the search.  They do not depend on the state, so one
+// block and one logarithm per lane serve 64 firings of the wavefront.
+struct dt_numbers {
+    double E, u;
+};
+
+__device__ __forceinline__ dt_numbers dt_draw64(uint32_t key0, uint32_t key1, uint32_t traj,
+                                                uint32_t net_id, uint32_t first,
+                                                unsigned long long* slow, uint32_t* sc)
 {
-    const rt_u4 w =
-        rt_philox4x32_10<false>(rt_u4{fired, 0xFFFFFFFFu, traj, net_id}, key0, key1);
-    *m2 = (((uint64_t)w.w << 32) | w.z) >> 11;
-    return rt_neglog_uniform((((uint64_t)w.y << 32) | w.x) >> 11, slow, sc);
+    const rt_u4 w = rt_philox4x32_10(rt_u4{first + threadIdx.x, 0xFFFFFFFFu, traj, net_id}, key0, key1);
+    dt_numbers d;
+    d.E = rt_neglog_wave((((uint64_t)w.y << 32) | w.x) >> 11, false, slow,
+                         rt_log_ctx<rt_log_const_tab>{{}, sc});
+    d.u = (double)(((((uint64_t)w.w << 32) | w.z) >> 11) + 1) * 0x1p-53;
+    return d;
+}
+
+__device__ __forceinline__ double dt_lane(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
 __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
@@ -669,8 +698,7 @@ __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
             __threadfence();                               // before the counts' atomics
         }
         double a0 = *root_d;
-        uint64_t m2 = 0;
-        double E1 = dt_draw(key0, key1, traj, net_id, 0u, &m2, &ws->slow_logs, log_scratch);
+        dt_numbers num = dt_draw64(key0, key1, traj, net_id, 0u, &ws->slow_logs, log_scratch);
 
         double t = 0.0, s_next = it->G > 0 ? rt_const(it->s)[0] : __builtin_inf();
         int32_t g = 0;
@@ -680,7 +708,7 @@ __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
 
         for (;;) {
             if (a0 == 0.0) { st = RTSSA_TRAJ_ABSORBED; break; }
-            const double t_new = t + E1 / a0;
+            const double t_new = t + dt_lane(num.E, (int)(fired & 63u)) / a0;
             if (t_new > t_end) break;
             while (s_next < t_new) {
                 if (it->samples) {
@@ -691,32 +719,47 @@ __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
                 s_next = g < it->G ? rt_const(it->s)[g] : __builtin_inf();
             }
             // ---- the search, from the root down (every lane alike)
-            double rem = (double)(m2 + 1) * 0x1p-53 * a0;
+            // A node's children are passed in order, each passed child
+            // subtracted (an empty one changes nothing): all eight remainders
+            // come from one chain of subtractions, the first positive child to
+            // hold its remainder from selects over independent compares.  With
+            // a found flag carried from child to child a level took twice as
+            // long (1000 species, 4000 channels, 512 trajectories: 189 ms a
+            // launch, 136 this way and with 64 firings' draws at once).
+            double rem = dt_lane(num.u, (int)(fired & 63u)) * a0;
             int j = 0;
 #pragma unroll
             for (int l = kMaxLevels; l >= 1; --l) {
                 if (l > top) continue;
                 const double2* vd = (const double2*)(tr.d[l - 1] + (j << 3));
-                double v[8];
+                double v[8], r8[8];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const double2 x = vd[i];
                     v[2 * i] = x.x;
                     v[2 * i + 1] = x.y;
                 }
-                int last = 0;
+                r8[0] = rem;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) last = v[i] > 0.0 ? i : last;
-                int take = last;
-                bool found = false;
+                for (int i = 1; i < 8; ++i) r8[i] = r8[i - 1] - v[i - 1];
+                int take = -1;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const bool hit = !found && v[i] > 0.0 && (rem <= v[i] || i == last);
+                for (int i = 7; i >= 0; --i) {
+                    const bool hit = v[i] > 0.0 && r8[i] <= v[i];
                     take = hit ? i : take;
-                    rem = found || hit ? rem : rem - v[i];
-                    found = found || hit;
+                    rem = hit ? r8[i] : rem;
                 }
-                j = __builtin_amdgcn_readfirstlane((j << 3) + take);
+                take = __builtin_amdgcn_readfirstlane(take);
+                if (__builtin_expect(take < 0, 0)) {
+                    // the remainder passes them all: the last positive child
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        take = v[i] > 0.0 ? i : take;
+                        rem = v[i] > 0.0 ? r8[i] : rem;
+                    }
+                    take = __builtin_amdgcn_readfirstlane(max(take, 0));
+                }
+                j = (j << 3) + take;
             }
             const int mu = j;
             // ---- mu's fixed-stride rows, then the touched channels' data
@@ -729,10 +772,10 @@ __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
             const int k = lane == 0 || !act ? mu : tv;
             const int2 rr0 = react[k];
             const double c0 = cc[k];
-            // the next firing's draws while the loads are in flight
-            uint64_t m2n;
-            const double E1n = dt_draw(key0, key1, traj, net_id, fired + 1u, &m2n,
-                                       &ws->slow_logs, log_scratch);
+            // (every 64th firing) the next firings' numbers while the loads are
+            // in flight
+            if ((fired & 63u) == 63u)
+                num = dt_draw64(key0, key1, traj, net_id, fired + 1u, &ws->slow_logs, log_scratch);
             // ---- the jump v_mu, checked against [0, 2^31 - 1]
             const int64_t xv = (int64_t)X[sp] + dl;
             const bool okl = !has_nu || (xv >= 0 && xv <= 0x7FFFFFFF);
@@ -774,8 +817,6 @@ __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
             t = t_new;
             ++fired;
             hash = (hash ^ (unsigned long long)(uint32_t)mu) * kFnvPrime;
-            E1 = E1n;
-            m2 = m2n;
             if (fired >= C.max_firings) { st = RTSSA_TRAJ_MAX_FIRINGS; break; }
         }
 
@@ -825,12 +866,32 @@ size_t rt_lazy_lds_bytes(int N, int M) { return tree_lds_bytes(N, M, kTopMax, kL
 // the sum tree goes up to its single root
 static size_t dmtree_lds_bytes(int N, int M) { return tree_lds_bytes(N, M, 1, kMaxLevels); }
 
+typedef void (*lazy_kernel_t)(rt_class_dev, rt_lazy_rec*, unsigned long long*, uint32_t*, int64_t);
+
+template <bool SCHED>
+static lazy_kernel_t lazy_pick(int chunks)
+{
+    return chunks <= 2 ? rt_lazy_kernel<SCHED, 2>
+                       : (chunks <= 4 ? rt_lazy_kernel<SCHED, 4> : rt_lazy_kernel<SCHED, 8>);
+}
+
+// The lazy kernel of a class: built for the chunks of its largest top level.  A
+// class's channel counts share a power-of-two range, so the largest network has
+// it (above 512 channels every tree has a node level).
+static lazy_kernel_t lazy_kernel_for(int max_M, bool sched)
+{
+    int top = std::max(max_M, 1);
+    while (top > kTopMax) top = (top + kFan - 1) >> kFanLog;
+    const int chunks = (top + 63) / 64;
+    return sched ? lazy_pick<true>(chunks) : lazy_pick<false>(chunks);
+}
+
 // The lazy kernel's grid: the requested one, or the resident wavefronts
 // (LDS-limited) of the device, never more than the trajectories.
 int rt_lazy_grid(int max_N, int max_M, int grid, int64_t units, bool sched, int* grid_out,
                  int max_per_cu)
 {
-    const void* fn = sched ? (const void*)rt_lazy_kernel<true> : (const void*)rt_lazy_kernel<false>;
+    const void* fn = (const void*)lazy_kernel_for(max_M, sched);
     const size_t lds = rt_lazy_lds_bytes(max_N, max_M);
     if (lds == 0) return rt_fail(RTSSA_E_UNSUPPORTED, "network too large for the lazy form");
     int dev = 0, lds_max = 0, cus = 0;
@@ -882,7 +943,7 @@ int rt_launch_lazy(const rt_class_dev& C, int max_N, int max_M, int grid, int64_
     }
     const size_t rec_bytes = (size_t)grid * m_stride * sizeof(rt_lazy_rec);
     const size_t word_bytes = (size_t)grid * m_stride * sizeof(unsigned long long);
-    auto* kern = sched ? rt_lazy_kernel<true> : rt_lazy_kernel<false>;
+    const lazy_kernel_t kern = lazy_kernel_for(max_M, sched);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64), lds, stream, C, (rt_lazy_rec*)wsp,
                        (unsigned long long*)((char*)wsp + rec_bytes),
                        (uint32_t*)((char*)wsp + rec_bytes + word_bytes), m_stride);
