@@ -2,6 +2,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "internal.h"
 #include "rt_device.h"
 #include "rt_wave.h"
@@ -9,6 +11,18 @@
 namespace {
 
 constexpr int kRedBlock = 256;
+
+// Sum of 256 values, one a thread, in a fixed tree; every thread gets it.
+__device__ __forceinline__ double block_sum(double v, double* sh)
+{
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    for (int w = kRedBlock / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    return sh[0];
+}
 
 // Deterministic block sum of f over a contiguous row chunk.
 __global__ __launch_bounds__(kRedBlock) void rt_sum_f_kernel(const double* f, int64_t R,
@@ -19,35 +33,36 @@ __global__ __launch_bounds__(kRedBlock) void rt_sum_f_kernel(const double* f, in
     const int64_t r1 = r0 + chunk < R ? r0 + chunk : R;
     double acc = 0.0;
     for (int64_t r = r0 + threadIdx.x; r < r1; r += kRedBlock) acc += f[r];
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = kRedBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+    acc = block_sum(acc, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = acc;
 }
 
 // Per block and channel: sum_r y_rk and sum_r y_rk^2 with
-// y_rk = (f_r - b_r)(n_rk - T_rk), b_r the leave-one-out mean of f.
+// y_rk = (f_r - b_r)(n_rk - T_rk), b_r the leave-one-out mean of f.  Reading n
+// and T bounds it (12 bytes a trajectory and channel); with a block for every
+// 4096 trajectories, whatever M, the device was nearly idle (20000 x 45: 5
+// blocks, 323 us; 110 blocks, 18 us).
 __global__ __launch_bounds__(kRedBlock) void rt_score_part_kernel(
     const double* f, const uint32_t* n, const double* T, int64_t R, int32_t M,
-    int32_t baseline, int64_t chunk, const double* fpart, int nb, double* out)
+    int32_t baseline, int64_t chunk, const double* fpart, int nbf, double* out)
 {
     __shared__ double s1[kRedBlock], s2[kRedBlock];
-    double F = 0.0;
-    for (int b = 0; b < nb; ++b) F += fpart[b];
+    const int tid = threadIdx.x;
+    const double F = block_sum(tid < nbf ? fpart[tid] : 0.0, s1);   // nbf <= 256
+    __syncthreads();
     const double denom = R > 1 ? (double)(R - 1) : 1.0;
     const int64_t r0 = (int64_t)blockIdx.x * chunk;
     const int64_t r1 = r0 + chunk < R ? r0 + chunk : R;
     const int kk = M < kRedBlock ? M : kRedBlock;
     const int tpk = kRedBlock / kk;
-    const int tid = threadIdx.x;
+    const int q = tid / kk;
+    int top = 1;                                           // smallest power of two >= tpk
+    while (top < tpk) top <<= 1;
     for (int kb = 0; kb < M; kb += kk) {
         const int k = kb + tid % kk;
-        const int q = tid / kk;
         double a1 = 0.0, a2 = 0.0;
         if (q < tpk && k < M) {
+#pragma unroll 4
             for (int64_t r = r0 + q; r < r1; r += tpk) {
                 const double fr = f[r];
                 const double b = baseline ? (F - fr) / denom : 0.0;
@@ -59,26 +74,37 @@ __global__ __launch_bounds__(kRedBlock) void rt_score_part_kernel(
         s1[tid] = a1;
         s2[tid] = a2;
         __syncthreads();
-        if (tid < kk && kb + tid < M) {
-            double t1 = 0.0, t2 = 0.0;
-            for (int qq = 0; qq < tpk; ++qq) { t1 += s1[qq * kk + tid]; t2 += s2[qq * kk + tid]; }
-            out[((int64_t)blockIdx.x * M + kb + tid) * 2 + 0] = t1;
-            out[((int64_t)blockIdx.x * M + kb + tid) * 2 + 1] = t2;
+        for (int h = top >> 1; h > 0; h >>= 1) {           // over q, in a fixed tree
+            if (q < h && q + h < tpk) {
+                s1[tid] += s1[tid + h * kk];
+                s2[tid] += s2[tid + h * kk];
+            }
+            __syncthreads();
+        }
+        if (tid < kk && k < M) {
+            out[((int64_t)blockIdx.x * M + k) * 2 + 0] = s1[tid];
+            out[((int64_t)blockIdx.x * M + k) * 2 + 1] = s2[tid];
         }
         __syncthreads();
     }
 }
 
-__global__ void rt_score_final_kernel(const double* part, int nb, int32_t M, int64_t R,
-                                      double* grad, double* se)
+// One block per channel: the sums of its block sums, in a fixed tree.
+__global__ __launch_bounds__(kRedBlock) void rt_score_final_kernel(const double* part, int nb,
+                                                                   int32_t M, int64_t R,
+                                                                   double* grad, double* se)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= M) return;
+    __shared__ double sh[kRedBlock];
+    const int k = blockIdx.x;
     double t1 = 0.0, t2 = 0.0;
-    for (int b = 0; b < nb; ++b) {
+    for (int b = threadIdx.x; b < nb; b += kRedBlock) {
         t1 += part[((int64_t)b * M + k) * 2 + 0];
         t2 += part[((int64_t)b * M + k) * 2 + 1];
     }
+    t1 = block_sum(t1, sh);
+    __syncthreads();
+    t2 = block_sum(t2, sh);
+    if (threadIdx.x != 0) return;
     const double Rd = (double)R;
     grad[k] = t1 / Rd;
     if (se) {
@@ -253,36 +279,42 @@ int rt_launch_debug_select(const double* v, int32_t M, int64_t count, int32_t ma
     return hipGetLastError() == hipSuccess ? RTSSA_OK : rt_fail(RTSSA_E_HIP, "launch failed");
 }
 
-// blocks of the score reduction: one per 4096 trajectories, 1..256
-static int score_blocks(int64_t R)
+// Blocks of the score reduction, a function of the sizes alone: of the sum of f,
+// one per 2048 trajectories, at most the 256 values a block adds; of the channel
+// sums, one per 8192 values of n, at most 1024 and one a trajectory.
+static int score_f_blocks(int64_t R)
 {
-    int64_t nb = (R + 4095) / 4096;
-    return (int)(nb > 256 ? 256 : (nb < 1 ? 1 : nb));
+    return (int)std::min<int64_t>(256, std::max<int64_t>(1, (R + 2047) / 2048));
+}
+
+static int score_blocks(int64_t R, int32_t M)
+{
+    const int64_t nb = R > (int64_t)(1024 * 8192) / M ? 1024 : (R * M + 8191) / 8192;
+    return (int)std::min<int64_t>(std::max<int64_t>(nb, 1), R);
 }
 
 size_t rt_score_grad_workspace_bytes(int64_t R, int32_t M)
 {
-    const size_t nb = (size_t)score_blocks(R);
-    return sizeof(double) * (nb + nb * (size_t)M * 2);
+    return sizeof(double) * ((size_t)score_f_blocks(R) + (size_t)score_blocks(R, M) * M * 2);
 }
 
 int rt_launch_score_grad(const double* f, const uint32_t* n, const double* T, int64_t R,
                          int32_t M, int32_t baseline, double* grad, double* se,
                          void* workspace, hipStream_t stream)
 {
-    const int nb = score_blocks(R);
-    const int64_t chunk = (R + nb - 1) / nb;
+    const int nbf = score_f_blocks(R), nb = score_blocks(R, M);
+    const int64_t chunk_f = (R + nbf - 1) / nbf, chunk = (R + nb - 1) / nb;
     double* buf = (double*)workspace;
     const size_t bytes = rt_score_grad_workspace_bytes(R, M);
     if (!buf && hipMallocAsync((void**)&buf, bytes, stream) != hipSuccess)
         return rt_fail(RTSSA_E_NOMEM, "score workspace allocation failed");
     double* fpart = buf;
-    double* part = buf + nb;
-    hipLaunchKernelGGL(rt_sum_f_kernel, dim3(nb), dim3(kRedBlock), 0, stream, f, R, chunk, fpart);
+    double* part = buf + nbf;
+    hipLaunchKernelGGL(rt_sum_f_kernel, dim3(nbf), dim3(kRedBlock), 0, stream, f, R, chunk_f, fpart);
     hipLaunchKernelGGL(rt_score_part_kernel, dim3(nb), dim3(kRedBlock), 0, stream, f, n, T, R, M,
-                       baseline, chunk, fpart, nb, part);
-    hipLaunchKernelGGL(rt_score_final_kernel, dim3((M + 255) / 256), dim3(256), 0, stream, part,
-                       nb, M, R, grad, se);
+                       baseline, chunk, fpart, nbf, part);
+    hipLaunchKernelGGL(rt_score_final_kernel, dim3(M), dim3(kRedBlock), 0, stream, part, nb, M, R,
+                       grad, se);
     hipError_t e = hipGetLastError();
     if (!workspace) hipFreeAsync(buf, stream);
     return e == hipSuccess ? RTSSA_OK : rt_fail(RTSSA_E_HIP, "score kernel launch failed");

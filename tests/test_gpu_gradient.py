@@ -165,3 +165,26 @@ def test_autograd_expectation():
     z = _z(3)                                   # the mean and two channels
     assert abs(float(loss.detach()) - m) < z * math.sqrt(m / w.R)
     assert np.all(np.abs(log_c.grad.numpy() - dm) < z * se.cpu().numpy())
+
+
+@pytest.mark.parametrize("R,M", [(1, 1), (1, 300), (2, 5), (255, 7), (256, 256), (257, 257),
+                                 (300, 1000), (5000, 64), (70001, 3), (600000, 2), (9000, 1100)])
+def test_score_grad_partitions(R, M):
+    """Sizes around the edges of the reduction's partitions: one row, more
+    channels than a block's threads, one and many blocks.  Every term is within
+    a few ulps and at most about 40 are added in one chain, so 1e-12 of the sum of
+    magnitudes bounds the difference to a float64 sum in any order."""
+    from paper_2103_00405_amd import api
+    gen = torch.Generator().manual_seed(R * 7 + M)
+    f = torch.rand(R, dtype=torch.float64, generator=gen) * 10
+    n = torch.randint(0, 50, (R, M), dtype=torch.int32, generator=gen)
+    T = torch.rand((R, M), dtype=torch.float64, generator=gen) * 50
+    g, se = (v.cpu() for v in api.score_grad(f.cuda(), n.cuda(), T.cuda()))
+    base = (f.sum() - f) / (R - 1) if R > 1 else torch.zeros_like(f) + f.sum() - f
+    y = (f - base)[:, None] * (n.double() - T)
+    assert bool(((g - y.mean(0)).abs() <= 1e-12 * y.abs().mean(0) + 1e-300).all())
+    if R > 1:
+        want = y.std(0) / R ** 0.5
+        assert bool(((se - want).abs() <= 1e-9 * want).all())
+    else:
+        assert not bool(se.any())
