@@ -47,14 +47,15 @@
 
 namespace {
 
-constexpr int kBlock = 128;
+// Threads of a workgroup, which shares one 6 KiB logarithm table: the size that
+// leaves a CU's LDS the most wavefronts (10 at 8 slots, 12 at 6, 16 below).
+constexpr int block_of(int S) { return S >= 8 ? 128 : 256; }
 
 // Draws are made once this many lanes of a wavefront wait for one.
 constexpr int kDrawLanes = 16;
 
-// Waves per SIMD the register allocation must allow (LDS allows 3 at 6 slots
-// and 2 at 8).
-constexpr int subwave_min_waves(int S, bool SCHED) { return S <= 4 ? 4 : 3; }
+// Waves per SIMD the register allocation must allow (no more fit in LDS).
+constexpr int subwave_min_waves(int S) { return S <= 5 ? 4 : 3; }
 
 // LDS bytes of one wavefront: per slot and lane a_k, the next draw, 1 / a_k
 // and n_k; then X of each group.
@@ -64,8 +65,9 @@ constexpr size_t wave_lds_bytes(int L, int S, int NP)
 }
 
 template <int L, int S, bool SCHED>
-__global__ __launch_bounds__(kBlock, subwave_min_waves(S, SCHED)) void rt_subwave_kernel(rt_class_dev C)
+__global__ __launch_bounds__(block_of(S), subwave_min_waves(S)) void rt_subwave_kernel(rt_class_dev C)
 {
+    constexpr int kBlock = block_of(S);
     constexpr int G = 64 / L;                              // groups of a wavefront
     constexpr int LOG2L = __builtin_ctz(L);
     constexpr int32_t kKey = 8 * L - 1;                    // channel bits of a selection key
@@ -441,11 +443,11 @@ subwave_kernel_t sw_pick(bool sched)
 subwave_kernel_t select_subwave(int L, int S, bool sched)
 {
 #define RT_CASE(l, s) if (L == l && S == s) return sw_pick<l, s>(sched);
-    RT_CASE(4, 2) RT_CASE(4, 4) RT_CASE(4, 6) RT_CASE(4, 8)
-    RT_CASE(8, 2) RT_CASE(8, 4) RT_CASE(8, 6) RT_CASE(8, 8)
-    RT_CASE(16, 2) RT_CASE(16, 4) RT_CASE(16, 6) RT_CASE(16, 8)
-    RT_CASE(32, 2) RT_CASE(32, 4) RT_CASE(32, 6) RT_CASE(32, 8)
-    RT_CASE(64, 2) RT_CASE(64, 4) RT_CASE(64, 6) RT_CASE(64, 8)
+    RT_CASE(4, 2) RT_CASE(4, 4) RT_CASE(4, 5) RT_CASE(4, 6) RT_CASE(4, 8)
+    RT_CASE(8, 2) RT_CASE(8, 4) RT_CASE(8, 5) RT_CASE(8, 6) RT_CASE(8, 8)
+    RT_CASE(16, 2) RT_CASE(16, 4) RT_CASE(16, 5) RT_CASE(16, 6) RT_CASE(16, 8)
+    RT_CASE(32, 2) RT_CASE(32, 4) RT_CASE(32, 5) RT_CASE(32, 6) RT_CASE(32, 8)
+    RT_CASE(64, 2) RT_CASE(64, 4) RT_CASE(64, 5) RT_CASE(64, 6) RT_CASE(64, 8)
 #undef RT_CASE
     return nullptr;
 }
@@ -479,11 +481,11 @@ int rt_subwave_auto_lanes(int M, int64_t units, int waves_per_cu)
     return L;
 }
 
-// Slots per lane: the fewest of 2, 4, 6, 8 that hold M channels (0: none).
+// Slots per lane: the fewest of 2, 4, 5, 6, 8 that hold M channels (0: none).
 int rt_subwave_slots(int M, int L)
 {
     const int s = (M + L - 1) / L;
-    return s <= 2 ? 2 : s <= 4 ? 4 : (s <= 6 ? 6 : (s <= 8 ? 8 : 0));
+    return s <= 2 ? 2 : (s <= 4 ? 4 : (s <= 6 ? s : (s <= 8 ? 8 : 0)));
 }
 
 int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStream_t stream,
@@ -497,6 +499,7 @@ int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStre
     // groups within 64 KiB
     if ((size_t)(256 / L) * (NP + L + MP) * 4 > 64 * 1024)
         return rt_fail(RTSSA_E_UNSUPPORTED, "sub-wave LDS too large");
+    const int kBlock = block_of(S);
     const size_t lds = (kBlock / 64) * wave_lds_bytes(L, S, NP);
     if (lds > 48 * 1024 &&
         hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,
