@@ -187,7 +187,9 @@ bool rt_rows_ready(const rtssa_network* net, int rows)
 
 int rt_rows_prepare(rtssa_network* net, int rows)
 {
-    if (rows >= 2) return rt_group_rows_prepare(net);
+    // (a network of the sub-wave mapping's sizes gets that mapping's records with
+    // the tree methods' rows: whoever built rows for one may run the other)
+    if (rows >= 2 || (rows == 1 && net->M <= 512)) return rt_group_rows_prepare(net);
     if (rows == 1) return rt_lazy_prepare(net);
     return RTSSA_OK;
 }

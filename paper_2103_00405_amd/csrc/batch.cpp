@@ -187,7 +187,7 @@ static int batch_create(const rtssa_batch_item* items, int32_t count, const rtss
             if (b.method == RTSSA_METHOD_DIRECT_TREE && (b.T_out || b.tie_step))
                 return rt_fail(RTSSA_E_INVALID, at + "the direct method has no T_out or tie_step");
             if (b.R > 0) {
-                rc = rt_lazy_prepare(const_cast<rtssa_network*>(b.net));
+                rc = rt_rows_prepare(const_cast<rtssa_network*>(b.net), 1);
                 if (rc) return rt_fail(rc, at + rtssa_last_error());
             }
         }

@@ -25,9 +25,10 @@
 //              group's mu fires before its draw is there;
 //   event      T_k += a_k Delta, T_mu = P_mu, P_mu += E (Eq. 15, 26), new a_k
 //              of D(mu) by the lanes holding its records, X + v_mu.
-// Measured (45 channels, 20000 trajectories, with the score gradient: 9.7 ms
-// before, 4.3 ms; 301 channels, 4000 trajectories: 44.8, 19.4 ms) against the
-// kernel this replaced, which kept a_k and 1 / a_k in registers, refreshed them
+// Measured (45 channels, 20000 trajectories, with the score gradient: 9.8 ms
+// before, 4.0 ms; 301 channels, 4000 trajectories: 44.8, 14.5 ms -- 20.4 at 6
+// slots and 12 wavefronts a CU, where 5 slots leave room for all 4000) against
+// the kernel this replaced, which kept a_k and 1 / a_k in registers, refreshed them
 // one stale slot at a time from the network tables, reduced (gap, second gap,
 // channel) in binary64 and made each draw in one lane a group.
 //

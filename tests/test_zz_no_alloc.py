@@ -118,3 +118,23 @@ def test_noalloc_refuses_a_workspace_and_unbuilt_rows():
                                       0, 0, 8, None, 0, 0, 0, *nulls,
                                       C.byref(Options(0, 0, 0, 0, 2)), stream, C.byref(Stats()))
     assert rc == -1 and b"rows built" in lib().rtssa_last_error()
+
+
+def test_noalloc_subwave_after_rows_built_for_the_lazy_form():
+    """Rows built for a tree method also serve the sub-wave mapping, which reads
+    the records beside them: the allocation-free call, which builds nothing,
+    runs it after a workspace query for the lazy form alone."""
+    from paper_2103_00405_amd import api
+    from paper_2103_00405_amd._lib import Options, check, lib
+    rng = np.random.default_rng(31)
+    spec = W.random_network(10, 40, rng, logc=(-1.0, 1.0), bimol_scale=0.05)
+    x0 = rng.integers(0, 60, size=10).astype(np.int32)
+    grid = np.linspace(0.0, 1.0, 4)
+    ref = api.simulate(api.Network(spec), x0, 1.0, grid, 50, seed=6, with_hash=True)
+    net = api.Network(spec)
+    nbytes = C.c_size_t()
+    check(lib().rtssa_workspace_size(net.handle, 50, C.byref(Options(0, 0, 0, 0, api.METHOD_LAZY)),
+                                     C.byref(nbytes)))
+    got, _ = _noalloc(net, torch.as_tensor(x0).cuda(), 1.0, torch.as_tensor(grid).cuda(), 50, 6, ref)
+    for k in got:
+        assert torch.equal(got[k], ref[k]), k
