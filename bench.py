@@ -29,25 +29,21 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# Algorithmic issue slots of one firing of a 3-channel, 2-species network
-# (full-rate VALU op = 1 slot; 32-bit integer products and v_rcp_f64 = 4):
-# per channel sub, mul, fma and about three compares or selects; the fired
-# channel's propensities with one division each (~13); one Philox4x32-10
-# block (~100 instructions, 20 multi-pass products), the 53-bit uniform (~6),
-# the correctly rounded log's fast path (~30) and bookkeeping (~15): about
-# 200 instructions = 240-270 slots, taken as 255.  This is the figure the
-# roofline fraction uses.
-ALG_SLOTS_PER_FIRING_LV = 255
-# The same firing itemised for this kernel's own code (reported beside it):
-# gaps 3x(sub, mul, max, cmp, 2 sel) 18; argmin with second minimum 15;
-# near-tie, time, termination and sample checks 6; internal-time update 9;
-# jump with overflow check 10; firing counts 6; Philox4x32-10 10x(2 products
-# x4 + 2 xor3) 100; 53-bit uniform 8; correctly rounded log fast phase 55; P
-# refresh 8; three propensities with reciprocals 51.
-ITEMISED_SLOTS_PER_FIRING_LV = 286
+# Algorithmic issue slots of one firing of a 3-channel, 2-species network in
+# the thread kernel (a full-rate wave64 VALU instruction = 1 slot of 4 cycles;
+# v_mad_u64_u32 = 2, v_rcp_f64 = 4, as measured): gaps 3 x (sub, conversion,
+# product, key) with binary32 1/a_k 22; argmin by med3 / min 6; the winner's
+# exact gap (selects and one exact reciprocal) 21; internal times 3; landing of
+# the fired channel's P and n 6; jump with overflow check 6; Philox4x32-10 58
+# (10 rounds of 2 wide products and 2 three-input xors, less the constant
+# words); 53-bit uniform 8; correctly rounded log, quick phase 33; three
+# propensities from the products of two species 12.  This is the figure the
+# roofline fraction uses.  (With an exact reciprocal per channel, 51 slots for
+# the propensities and the log's double-double phase a firing took 255.)
+ALG_SLOTS_PER_FIRING_LV = 175
 # Instructions the profiler counts per firing of the headline kernel
 # (SQ_INSTS_VALU x 64 / firings; profiles/rt_thread_kernel_lv_ensemble_sq_counters.md).
-ISSUED_VALU_PER_FIRING_LV = 307
+ISSUED_VALU_PER_FIRING_LV = 197
 
 
 # Algorithmic lane-ops of one firing of an M-channel network in the eager
@@ -59,13 +55,6 @@ def alg_lane_ops_eager(M, deps=20):
     return 6 * M + 600 + 13 * deps + 150
 
 
-# The same firing itemised for the workgroup kernel's code (reported beside
-# it): per channel T update (1), gap (sub, mul, max, cmp, 2 sel = 6), argmin
-# with second minimum (5); the draw (~163) and the dependents (~17 each).
-def itemised_slots_group(M, deps=20):
-    return 12 * M + 163 + 17 * deps
-
-
 CLOCK_HZ = 2.4e9
 PEAK_LANE_SLOTS = 256 * 4 * 16 * CLOCK_HZ   # CUs x SIMDs x lanes x clock = 3.93e13 /s
 
@@ -73,14 +62,14 @@ PEAK_LANE_SLOTS = 256 * 4 * 16 * CLOCK_HZ   # CUs x SIMDs x lanes x clock = 3.93
 # from two rocprofv3 counter passes (FETCH_SIZE, WRITE_SIZE) scaled by the same
 # counters on a 1 GiB copy (factors 2.0 and 1.0).  Valid for the kernel as
 # profiled; set to None when the kernel changes until it is measured again.
-LV_TRAFFIC_BYTES_PER_LAUNCH = 1.331e+09
+LV_TRAFFIC_BYTES_PER_LAUNCH = 8.341e+09
 
 # VALU instructions (wave64) of one step of the batched workload: SQ_INSTS_VALU
-# summed over the timed replay's ten class kernels in one rocprofv3 counter
+# summed over the timed replay's eleven class kernels in one rocprofv3 counter
 # pass.  At 4 cycles per instruction on 256 x 4 SIMDs the step cannot take
 # less than this many cycles' worth of issue; valid for the kernels and the
 # autotuner's plan as profiled, None when they change until measured again.
-BATCH_VALU_INSTR_PER_STEP = 6.217e+11
+BATCH_VALU_INSTR_PER_STEP = 4.200e+11
 SIMD_ISSUE_HZ = 256 * 4 * CLOCK_HZ / 4        # wave64 VALU instructions per second
 
 
@@ -314,7 +303,6 @@ def bench_large(api, W, steps, warmup, cpu_s=0.0):
             "roofline": {"bound": "alu", "achieved": ach / 1e12, "peak": PEAK_LANE_SLOTS / 1e12,
                          "unit": "Tslot/s", "frac": ach / PEAK_LANE_SLOTS,
                          "slots_per_firing": slots,
-                         "itemised_slots_per_firing": itemised_slots_group(w.net.M),
                          "kernel_ms": r["kernel_s"] * 1e3}}
 
 
@@ -607,9 +595,6 @@ def main():
                      "traffic_unit": "B per launch",
                      "kernel": "rt_thread_kernel<3,2>", "kernel_ms": r["kernel_s"] * 1e3,
                      "slots_per_firing": ALG_SLOTS_PER_FIRING_LV,
-                     "itemised_slots_per_firing": ITEMISED_SLOTS_PER_FIRING_LV,
-                     "frac_itemised": ITEMISED_SLOTS_PER_FIRING_LV * r["firings_per_step"] /
-                     r["kernel_s"] / PEAK_LANE_SLOTS,
                      "issued_valu_per_firing_profiled": ISSUED_VALU_PER_FIRING_LV},
         "firings_per_step": r["firings_per_step"],
         "near_ties": st["near_ties"],
