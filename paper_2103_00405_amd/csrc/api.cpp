@@ -71,7 +71,7 @@ int rt_launch_class(int mapping, int max_M, int max_N, int max_nu, const rt_clas
     if (method != RTSSA_METHOD_RANDOM_TIME)
         return rt_fail(RTSSA_E_UNSUPPORTED, "the direct method runs only in the thread mapping");
     if (mapping == RTSSA_MAP_WAVE) {
-        int L = block > 0 ? block : rt_subwave_auto_lanes(max_M, lanes, 4);
+        int L = block > 0 ? block : rt_subwave_auto_lanes(max_M, max_N, lanes, 4);
         while (L < 64 && L < max_nu) L <<= 1;
         if (L != 4 && L != 8 && L != 16 && L != 32 && L != 64)
             return rt_fail(RTSSA_E_INVALID, "sub-wave lanes per trajectory must be 4..64, a power of 2");

@@ -101,8 +101,10 @@ class_key classify(const rtssa_network* net, int method, const std::vector<plan_
         mapping = RTSSA_MAP_WORKGROUP;
     if (mapping == RTSSA_MAP_WAVE) {
         int L = plan_lookup(plan, RTSSA_MAP_WAVE, net->M);
-        if (L <= 0) L = rt_subwave_auto_lanes(net->M, wave_units, kBatchWavesPerCu);
-        while (L < 64 && (L < net->max_nu || L * 8 < net->M)) L <<= 1;
+        if (L <= 0) L = rt_subwave_auto_lanes(net->M, net->N, wave_units, kBatchWavesPerCu);
+        while (L < 64 && (L < net->max_nu || L * 8 < net->M ||
+                          !rt_subwave_fits(net->M, net->N, L)))
+            L <<= 1;
         // two slot ranges a lane count: one class runs its small networks through
         // the slots of its largest, a class per slot count leaves the graph more
         // branches than the device has queues (192 / 400 / 800 random networks:

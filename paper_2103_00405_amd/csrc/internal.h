@@ -187,7 +187,8 @@ int rt_group_slots(int M, int L);
 // true when a workgroup kernel with L threads exists for M channels
 bool rt_group_supported(int M, int L);
 size_t rt_group_lds_bytes(int N, int M, int L);
-int rt_subwave_auto_lanes(int M, int64_t units, int waves_per_cu);
+int rt_subwave_auto_lanes(int M, int N, int64_t units, int waves_per_cu);
+bool rt_subwave_fits(int M, int N, int L);
 int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStream_t stream,
                       int* grid_used);
 // the workgroup mapping with the propensities in LDS (kernels_group_lds.hip):

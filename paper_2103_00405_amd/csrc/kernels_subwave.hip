@@ -464,14 +464,55 @@ int rt_subwave_lanes(int M)
     return L;
 }
 
+// Slots per lane: the fewest of 2, 4, 5, 6, 8 that hold M channels (0: none).
+int rt_subwave_slots(int M, int L)
+{
+    const int s = (M + L - 1) / L;
+    return s <= 2 ? 2 : (s <= 4 ? 4 : (s <= 6 ? s : (s <= 8 ? 8 : 0)));
+}
+
+// LDS bytes of a workgroup: the dynamic part the launch asks for, and with the
+// logarithm table and the wavefronts' shares.
+static size_t dynamic_lds_bytes(int L, int S, int N)
+{
+    return (size_t)(block_of(S) / 64) * wave_lds_bytes(L, S, (N + 3) & ~3);
+}
+
+static size_t group_lds_bytes(int L, int S, int N)
+{
+    const size_t fixed = block_of(S) == 128 ? sizeof(rt_log_lds<2>) + 2 * sizeof(rt_wave_share)
+                                            : sizeof(rt_log_lds<4>) + 4 * sizeof(rt_wave_share);
+    return (fixed + 15) / 16 * 16 + dynamic_lds_bytes(L, S, N);
+}
+
+// A workgroup's LDS limit (0: no device answers).
+static size_t lds_limit()
+{
+    int dev = 0, bytes = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&bytes, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+        return 0;
+    return (size_t)bytes;
+}
+
+// Whether L lanes a trajectory leave room for N species beside any network of
+// M's slot range (a batch's class runs its networks with the most slots of one
+// and the most species of another).  A launch that fits at L fits at 2 L.
+bool rt_subwave_fits(int M, int N, int L)
+{
+    const size_t limit = lds_limit();
+    return limit == 0 || group_lds_bytes(L, rt_subwave_slots(M, L) <= 4 ? 4 : 6, N) <= limit;
+}
+
 // Lanes per trajectory when nothing else says: as many as keep the units'
-// wavefronts within waves_per_cu, at least 8 and rt_subwave_lanes.  More lanes
-// are fewer slots and fewer groups a wavefront, so a faster firing, while a
-// wavefront has its SIMD to itself; on a full device fewer lanes do more per
-// instruction (45 channels, lanes 8 / 16 / 32 / 64: 300 trajectories 3.7 / 2.8
+// wavefronts within waves_per_cu, at least 8 and rt_subwave_lanes, and as many
+// as the species need to fit (whether a network runs does not depend on the
+// units).  More lanes are fewer slots and fewer groups a wavefront, so a faster
+// firing, while a wavefront has its SIMD to itself; on a full device fewer lanes
+// do more per instruction (45 channels, lanes 8 / 16 / 32 / 64: 300 trajectories 3.7 / 2.8
 // / 2.6 / 2.4 ms, 3000 3.8 / 2.9 / 3.4 / 3.7 ms, 30000 7.2 / 8.9 / 13.4 / 22.6
 // ms; 20 channels at 4 lanes: 2.6, 2.7 and 3.3 ms against 1.7, 1.7 and 2.7 at 8).
-int rt_subwave_auto_lanes(int M, int64_t units, int waves_per_cu)
+int rt_subwave_auto_lanes(int M, int N, int64_t units, int waves_per_cu)
 {
     int L = std::max(8, rt_subwave_lanes(M));
     int dev = 0, cus = 256;
@@ -479,14 +520,8 @@ int rt_subwave_auto_lanes(int M, int64_t units, int waves_per_cu)
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return L;
     while (L < 64 && units * (2 * L) <= (int64_t)cus * waves_per_cu * 64) L <<= 1;
+    while (L < 64 && !rt_subwave_fits(M, N, L)) L <<= 1;
     return L;
-}
-
-// Slots per lane: the fewest of 2, 4, 5, 6, 8 that hold M channels (0: none).
-int rt_subwave_slots(int M, int L)
-{
-    const int s = (M + L - 1) / L;
-    return s <= 2 ? 2 : (s <= 4 ? 4 : (s <= 6 ? s : (s <= 8 ? 8 : 0)));
 }
 
 int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStream_t stream,
@@ -495,13 +530,12 @@ int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStre
     const int S = rt_subwave_slots(max_M, L);
     subwave_kernel_t kfn = select_subwave(L, S, C.has_schedule != 0);
     if (!kfn) return rt_fail(RTSSA_E_UNSUPPORTED, "no sub-wave kernel for this size");
-    const int NP = (C.max_N + 3) & ~3, MP = (C.max_M + 3) & ~3;
-    // the networks taken: X, one word per lane and one per channel of 256 lanes'
-    // groups within 64 KiB
-    if ((size_t)(256 / L) * (NP + L + MP) * 4 > 64 * 1024)
+    const size_t limit = lds_limit();
+    if (limit == 0) return rt_fail(RTSSA_E_HIP, "device query failed");
+    if (group_lds_bytes(L, S, C.max_N) > limit)
         return rt_fail(RTSSA_E_UNSUPPORTED, "sub-wave LDS too large");
     const int kBlock = block_of(S);
-    const size_t lds = (kBlock / 64) * wave_lds_bytes(L, S, NP);
+    const size_t lds = dynamic_lds_bytes(L, S, C.max_N);
     if (lds > 48 * 1024 &&
         hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)
