@@ -79,7 +79,12 @@ typedef struct {
     uint64_t firings;         /* applied events over all trajectories */
     uint64_t near_ties;       /* applied events with a near-tie (see above) */
     uint64_t clamps;          /* applied events whose raw gap was negative */
-    uint64_t slow_logs;       /* Exp(1) draws that needed the accurate log phase */
+    uint64_t slow_logs;       /* Exp(1) draws that needed the accurate log phase, each
+                               * counted once: E(k, 0) .. E(k, n_k) of every channel, for
+                               * the direct methods the waiting times of events
+                               * 0 .. sum_k n_k; the thread mapping, which makes every draw
+                               * a firing ahead, counts one more of each (and an event that
+                               * overflows may add its own) */
     uint64_t status_count[4]; /* trajectories per end state */
     double kernel_ms;         /* device time of the simulation launch(es) */
     int32_t mapping;          /* mapping that ran */

@@ -165,8 +165,10 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                 m1 = (((uint64_t)w.w << 32) | w.z) >> 11;
             }
             // a padding slot (k >= M) keeps P = +inf: its gap is +inf in the pass
+            bool acc;
             const double e0 = rt_neglog_wave(m0, false, &ws->slow_logs, sc);
-            const double p1 = rt_neglog_wave(m1, false, &ws->slow_logs, sc);
+            const double e1 = rt_neglog_wave(m1, false, &ws->slow_logs, sc, &acc);
+            const double p1 = rt_mark_draw(e1, acc);
             const double p0 = live ? e0 : __builtin_inf();
             pa[k] = an;
             pinv[k] = __builtin_amdgcn_rcpf((float)an);
@@ -343,7 +345,9 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                 const uint64_t m = has ? rt_draw_m53<false>(key0, key1, traj, net_id,
                                                             (uint32_t)(tid + s1 * L), n1 + 1u)
                                        : 0x1FFFFFFFFFFFFFull;
-                const double E = rt_neglog_wave(m, false, &ws->slow_logs, sc);
+                bool acc;
+                double E = rt_neglog_wave(m, false, &ws->slow_logs, sc, &acc);
+                E = rt_mark_draw(E, acc);
 #pragma unroll
                 for (int s = 0; s < S; ++s) En[s] = (has && s == s1) ? E : En[s];
                 pending &= ~(has ? 1u << s1 : 0u);
@@ -391,7 +395,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                     // directly rather than selecting over every slot)
                     const double pm = P[sm];
                     T[sm] = pm;
-                    P[sm] = pm + En[sm];
+                    P[sm] = pm + fabs(En[sm]);
                     ++nk[sm];
                 } else {
                     // (with the schedule's registers the indexed form would
@@ -400,7 +404,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                     for (int s = 0; s < S; ++s)
                         if (s == sm) {
                             T[s] = P[s];
-                            P[s] = P[s] + En[s];
+                            P[s] = P[s] + fabs(En[s]);
                             ++nk[s];
                         }
                 }
@@ -474,6 +478,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
             }
         }
         const double dt = t_end - t;
+        unsigned long long left = 0ull;                      // marked draws that no firing took
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const int k = tid + s * L;
@@ -482,8 +487,10 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                 if (good) T[s] = fma(pa[k], dt, T[s]);
                 if (it->n_out) it->n_out[r * M + k] = nk[s];
                 if (it->T_out) it->T_out[r * M + k] = T[s];
+                if (!((pending >> s) & 1u) && En[s] < 0.0) ++left;
             }
         }
+        if (left) atomicAdd(&ws->slow_logs, 0ull - left);
         if (it->x_final)
             for (int j = tid; j < N; j += L) it->x_final[r * N + j] = Xf[j];
         if (tid == 0) {

@@ -594,20 +594,22 @@ __device__ __forceinline__ double dt_sum_node(const lazy_tree& tr, int l, int j)
 
 // The numbers of 64 consecutive firings, one firing a lane: E = RN(-ln u1) and
 // u2 = (m + 1) 2^-53 of the search.  They do not depend on the state, so one
-// block and one logarithm per lane serve 64 firings of the wavefront.
+// block and one logarithm per lane serve 64 firings of the wavefront.  u is
+// negative where the logarithm took the accurate phase (counted once a trajectory
+// has come to that firing).
 struct dt_numbers {
     double E, u;
 };
 
 __device__ __forceinline__ dt_numbers dt_draw64(uint32_t key0, uint32_t key1, uint32_t traj,
-                                                uint32_t net_id, uint32_t first,
-                                                unsigned long long* slow, uint32_t* sc)
+                                                uint32_t net_id, uint32_t first, uint32_t* sc)
 {
     const rt_u4 w = rt_philox4x32_10(rt_u4{first + threadIdx.x, 0xFFFFFFFFu, traj, net_id}, key0, key1);
     dt_numbers d;
-    d.E = rt_neglog_wave((((uint64_t)w.y << 32) | w.x) >> 11, false, slow,
-                         rt_log_ctx<rt_log_const_tab>{{}, sc});
-    d.u = (double)(((((uint64_t)w.w << 32) | w.z) >> 11) + 1) * 0x1p-53;
+    bool acc;
+    d.E = rt_neglog_wave((((uint64_t)w.y << 32) | w.x) >> 11, false, nullptr,
+                         rt_log_ctx<rt_log_const_tab>{{}, sc}, &acc);
+    d.u = rt_mark_draw((double)(((((uint64_t)w.w << 32) | w.z) >> 11) + 1) * 0x1p-53, acc);
     return d;
 }
 
@@ -698,7 +700,7 @@ __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
             __threadfence();                               // before the counts' atomics
         }
         double a0 = *root_d;
-        dt_numbers num = dt_draw64(key0, key1, traj, net_id, 0u, &ws->slow_logs, log_scratch);
+        dt_numbers num = dt_draw64(key0, key1, traj, net_id, 0u, log_scratch);
 
         double t = 0.0, s_next = it->G > 0 ? rt_const(it->s)[0] : __builtin_inf();
         int32_t g = 0;
@@ -726,7 +728,7 @@ __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
             // a found flag carried from child to child a level took twice as
             // long (1000 species, 4000 channels, 512 trajectories: 189 ms a
             // launch, 136 this way and with 64 firings' draws at once).
-            double rem = dt_lane(num.u, (int)(fired & 63u)) * a0;
+            double rem = fabs(dt_lane(num.u, (int)(fired & 63u))) * a0;
             int j = 0;
 #pragma unroll
             for (int l = kMaxLevels; l >= 1; --l) {
@@ -774,8 +776,10 @@ __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
             const double c0 = cc[k];
             // (every 64th firing) the next firings' numbers while the loads are
             // in flight
-            if ((fired & 63u) == 63u)
-                num = dt_draw64(key0, key1, traj, net_id, fired + 1u, &ws->slow_logs, log_scratch);
+            if ((fired & 63u) == 63u) {
+                if (num.u < 0.0) atomicAdd(&ws->slow_logs, 1ull);
+                num = dt_draw64(key0, key1, traj, net_id, fired + 1u, log_scratch);
+            }
             // ---- the jump v_mu, checked against [0, 2^31 - 1]
             const int64_t xv = (int64_t)X[sp] + dl;
             const bool okl = !has_nu || (xv >= 0 && xv <= 0x7FFFFFFF);
@@ -829,6 +833,11 @@ __global__ __launch_bounds__(64) void rt_dmtree_kernel(rt_class_dev C)
         }
         if (it->x_final)
             for (int j = lane; j < N; j += 64) it->x_final[r * N + j] = X[j];
+        // the waiting times up to firing `fired` (an overflow at a batch's last
+        // firing leaves the next batch in num)
+        if (num.u < 0.0 && lane <= (int)(fired & 63u) &&
+            !(st == RTSSA_TRAJ_OVERFLOW && (fired & 63u) == 63u))
+            atomicAdd(&ws->slow_logs, 1ull);
         if (lane == 0) {
             if (it->t_last) it->t_last[r] = t;
             if (it->status) it->status[r] = (uint8_t)st;

@@ -204,8 +204,10 @@ __global__ __launch_bounds__(block_of(S), subwave_min_waves(S)) void rt_subwave_
             if (waiting != 0u) {
                 const int s1 = need ? sm : __builtin_ctz(waiting);
                 const uint32_t n1 = lnk[s1 * 64] + 1u;
-                le[s1 * 64] = rt_exp1_wave(key0, key1, traj, net_id, (uint32_t)(s1 * L + li), n1,
-                                           &ws->slow_logs, sc);
+                bool acc;
+                const double E = rt_exp1_wave(key0, key1, traj, net_id, (uint32_t)(s1 * L + li), n1,
+                                              &ws->slow_logs, sc, &acc);
+                le[s1 * 64] = rt_mark_draw(E, acc);
                 waiting &= ~(1u << s1);
             }
         }
@@ -257,6 +259,7 @@ __global__ __launch_bounds__(block_of(S), subwave_min_waves(S)) void rt_subwave_
                     }
                 }
                 const double dt = t_end - t;
+                unsigned long long left = 0ull;              // marked draws that no firing took
 #pragma unroll
                 for (int s = 0; s < S; ++s) {
                     const int k = li + s * L;
@@ -264,8 +267,10 @@ __global__ __launch_bounds__(block_of(S), subwave_min_waves(S)) void rt_subwave_
                         if (good) T[s] = fma(la[s * 64], dt, T[s]);
                         if (it->n_out) it->n_out[r * M + k] = lnk[s * 64];
                         if (it->T_out) it->T_out[r * M + k] = T[s];
+                        if (!((waiting >> s) & 1u) && le[s * 64] < 0.0) ++left;
                     }
                 }
+                if (left) atomicAdd(&ws->slow_logs, 0ull - left);
                 if (it->x_final)
                     for (int j = li; j < N; j += L) it->x_final[r * N + j] = X[j];
                 if (li == 0) {
@@ -320,8 +325,10 @@ __global__ __launch_bounds__(block_of(S), subwave_min_waves(S)) void rt_subwave_
                                 rt_philox4x32_10(rt_u4{0u, (uint32_t)k, traj, net_id}, key0, key1);
                             p0 = rt_neglog_wave((((uint64_t)w.y << 32) | w.x) >> 11, false,
                                                 &ws->slow_logs, sc);
-                            le[s1 * 64] = rt_neglog_wave((((uint64_t)w.w << 32) | w.z) >> 11, false,
-                                                         &ws->slow_logs, sc);
+                            bool acc;
+                            const double e1 = rt_neglog_wave((((uint64_t)w.w << 32) | w.z) >> 11,
+                                                             false, &ws->slow_logs, sc, &acc);
+                            le[s1 * 64] = rt_mark_draw(e1, acc);
                             const double c = rt_const(it->net.c)[k];
                             an = rt_propensity_mem(rt_const(it->net.react)[k], c, X);
                             plain = plain && rt_plain_rate(c);

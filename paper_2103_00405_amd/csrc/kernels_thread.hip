@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
 #pragma unroll
         for (int j = 0; j < NT; ++j) X[j] = 0;
 #pragma unroll
-        for (int k = 0; k < MT; ++k) { T[k] = 0.0; Pk[k] = 0.0; a[k] = 0.0; }
+        for (int k = 0; k < MT; ++k) { T[k] = 0.0; Pk[k] = 1.0; a[k] = 0.0; }   // (padding: gap +inf)
         double t = 0.0, s_next = __builtin_inf();
         // the earliest of the next sample point, the next rate breakpoint and
         // t_end: a firing past it needs the rare branch (so does every pass of
@@ -313,6 +313,10 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
         uint32_t mu_p = 0u, n_next = 1u;                   // the draw to be made: E(mu_p, n_next)
         double E_now = 0.0, u_now = 0.0;                   // DIRECT: this firing's numbers
         float g_min = plain ? 1e-30f : __builtin_inff();   // smallest gap the binary32 order takes
+        // this pass makes draws again that are counted already (all the wavefront's:
+        // the one before ended a trajectory or a piece, and a trajectory's first
+        // pass makes E(0, 1))
+        bool again = true;
         while (active) {
             double df[MT];
             float gf[MT];
@@ -411,7 +415,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
             if (opens != 0ull) {
                 if (open) {
                     double u2;
-                    if (rt_neglog_open(draw_bits(u2), false, sc.sc, E_new))
+                    if (rt_neglog_open(draw_bits(u2), false, sc.sc, E_new) && !again)
                         atomicAdd(&ws->slow_logs, 1ull);
                 }
             }
@@ -573,7 +577,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                             // first internal firing times E(k, 0) and next draws
                             // E(k, 1): the two words of one block, a channel at a time
 #pragma unroll 1
-                            for (int k = 0; k < MT; ++k) {
+                            for (int k = 0; k < M; ++k) {
                                 const rt_u4 w =
                                     rt_philox_traj(tw, 0u, (uint32_t)k, net_k1, key0, key1);
                                 const double E0 = rt_neglog_wave(rt_block_m53(w, 0u), false,
@@ -593,12 +597,14 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                     }
                 }
                 // started lanes (and lanes past a breakpoint) compute their gaps
+                again = true;
                 if (__ballot(stop || brk) != 0ull) continue;
                 // the event is applied below
                 if (near_tie) atomicAdd(&ws->near_ties, 1ull);
                 if (clamped) atomicAdd(&ws->clamps, 1ull);
             }
             }
+            again = false;
             t = t_new;
             ++fired;
             if (want_hash) hash = (hash ^ (unsigned long long)(uint32_t)mu) * kFnvPrime;

@@ -108,12 +108,24 @@ __device__ __forceinline__ bool rt_plain_rate(double c)
     return c == 0.0 || (c >= 0x1p-100 && c <= 0x1p60);
 }
 
-// A firing channel's internal times: T = P, then P += E.  In place (the
-// compiler adds into a temporary and copies) and never as selects.
+// A firing channel's internal times: T = P, then P += |E| (a draw waiting for
+// its firing carries a mark in its sign, rt_mark_draw).  In place (the compiler
+// adds into a temporary and copies) and never as selects.
 __device__ __forceinline__ void rt_land(double& T, double& P, double E)
 {
     asm volatile("v_mov_b64 %0, %1" : "=v"(T) : "v"(P));
-    asm volatile("v_add_f64 %0, %0, %1" : "+v"(P) : "v"(E));
+    asm volatile("v_add_f64 %0, %0, |%1|" : "+v"(P) : "v"(E));
+}
+
+// A draw made ahead of its firing (sub-wave and workgroup kernels): negative when
+// it took the accurate phase.  Such a draw is counted when it is made and, should
+// the trajectory end without taking it, taken off again at the end (which draws
+// are ever made ahead depends on the wavefront's other trajectories; which are
+// taken does not).  The kernel adds |E| when the channel fires, a modifier of the
+// addition.
+__device__ __forceinline__ double rt_mark_draw(double E, bool accurate)
+{
+    return accurate ? -E : E;
 }
 
 // The near-tie rule (Eq. 4 gives ties probability zero; in binary64 the two
@@ -299,9 +311,8 @@ __device__ __forceinline__ bool rt_neglog_open(uint64_t m, bool force_accurate, 
 }
 
 // RN(-ln u) for the wave's active lanes; each lane that needs the accurate
-// phase adds one to the device counter *slow, or, with slow = NULL, sets
-// *took_slow instead (for a draw that may be discarded and counted only once
-// it is used).
+// phase adds one to the device counter *slow and sets *took_slow (either may be
+// NULL).
 template <class Tab>
 __device__ __forceinline__ double rt_neglog_wave(uint64_t m, bool force_accurate,
                                                  unsigned long long* slow,
@@ -360,9 +371,10 @@ template <class Tab>
 __device__ __forceinline__ double rt_exp1_wave(uint32_t k0, uint32_t k1, uint32_t traj,
                                                uint32_t net, uint32_t k, uint32_t n,
                                                unsigned long long* slow,
-                                               const rt_log_ctx<Tab>& lc)
+                                               const rt_log_ctx<Tab>& lc,
+                                               bool* took_slow = nullptr)
 {
-    return rt_neglog_wave(rt_draw_m53(k0, k1, traj, net, k, n), false, slow, lc);
+    return rt_neglog_wave(rt_draw_m53(k0, k1, traj, net, k, n), false, slow, lc, took_slow);
 }
 
 // E for channel k at firing index n, computed by every active lane alike.
