@@ -65,7 +65,7 @@ int rt_launch_class(int mapping, int max_M, int max_N, int max_nu, const rt_clas
                     int* grid_used, int method)
 {
     if (mapping == RTSSA_MAP_THREAD) {
-        *block_used = block;
+        *block_used = std::max(block, 0);
         return rt_launch_thread(max_M, max_N, C, block_used, grid, stream, grid_used, lanes, method);
     }
     if (method != RTSSA_METHOD_RANDOM_TIME)

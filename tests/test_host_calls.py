@@ -127,3 +127,13 @@ def test_subwave_refuses_species_past_the_lds(fake_hip):
 net = h.network(64, 12000)
 result = [(h.simulate(net, 12000, R, mapping=WAVE), h.error()) for R in (1, 30000)]
 """) == [[-2, "sub-wave LDS too large"]] * 2
+
+
+@pytest.mark.parametrize("mapping,method", [(THREAD, 0), (0, 1), (WAVE, 0), (WORKGROUP, 0)])
+def test_a_block_below_one_is_the_mapping_s_own(fake_hip, mapping, method):
+    got = _child(fake_hip, """
+net = h.network(3, 2)
+result = [(h.simulate(net, 2, 5000, mapping=%d, method=%d, block=b), h.counter('last_block').value)
+          for b in (0, -1, -64, -2147483648)]
+""" % (mapping, method))
+    assert got == [got[0]] * 4 and got[0][0] == 0
