@@ -137,3 +137,14 @@ result = [(h.simulate(net, 2, 5000, mapping=%d, method=%d, block=b), h.counter('
           for b in (0, -1, -64, -2147483648)]
 """ % (mapping, method))
     assert got == [got[0]] * 4 and got[0][0] == 0
+
+
+@pytest.mark.parametrize("M", [9, 200, 512])
+def test_subwave_rows_are_one_allocation_and_one_copy(fake_hip, M):
+    assert _child(fake_hip, """
+net = h.network(%d, 40)
+mallocs, copies = h.counter('mallocs').value, h.counter('copies').value
+opt, need = h.types.Options(mapping=WAVE), C.c_size_t()
+result = [h.lib.rtssa_workspace_size(net, 10, C.byref(opt), C.byref(need)),
+          h.counter('mallocs').value - mallocs, h.counter('copies').value - copies]
+""" % M) == [0, 1, 1]
