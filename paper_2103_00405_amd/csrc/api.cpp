@@ -187,11 +187,13 @@ bool rt_rows_ready(const rtssa_network* net, int rows)
 
 int rt_rows_prepare(rtssa_network* net, int rows)
 {
-    // (a network of the sub-wave mapping's sizes gets that mapping's records with
-    // the tree methods' rows: whoever built rows for one may run the other)
-    if (rows >= 2 || (rows == 1 && net->M <= 512)) return rt_group_rows_prepare(net);
-    if (rows == 1) return rt_lazy_prepare(net);
-    return RTSSA_OK;
+    if (rt_rows_ready(net, rows)) return RTSSA_OK;
+    if (rows >= 2) return rt_group_rows_prepare(net);
+    // a network of the sub-wave mapping's sizes gets that mapping's records with
+    // the tree methods' rows (whoever built rows for one may run the other),
+    // where there is memory for them: the tree methods do not read them
+    if (net->M <= 512 && rt_group_rows_prepare(net) == RTSSA_OK) return RTSSA_OK;
+    return rt_lazy_prepare(net);
 }
 
 int rt_check_method(const rtssa_network* net, const rtssa_options& o, bool want_T,

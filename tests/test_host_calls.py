@@ -139,6 +139,31 @@ result = [(h.simulate(net, 2, 5000, mapping=%d, method=%d, block=b), h.counter('
     assert got == [got[0]] * 4 and got[0][0] == 0
 
 
+def test_tree_methods_run_without_memory_for_the_records(fake_hip):
+    """The tree methods need their rows (about 256 bytes a channel) but not the
+    eager mappings' records (2 KiB a channel) built beside them: with memory
+    for the rows alone they run, and a call that must not allocate does not try."""
+    got = _child(fake_hip, """
+net = h.network(400, 100)
+limit, mallocs = h.counter('malloc_limit', C.c_size_t), h.counter('mallocs')
+limit.value = 400 * 64 * 16
+need = C.c_size_t()
+opt = h.types.Options(method=LAZY)
+result = [h.lib.rtssa_workspace_size(net, 10, C.byref(opt), C.byref(need))]
+before = mallocs.value
+result.append(h.simulate(net, 100, 1, entry='rtssa_simulate_noalloc', method=LAZY))
+ws = np.zeros(need.value + 512, np.uint8)
+at = (ws.ctypes.data + 255) // 256 * 256
+result.append(h.simulate(net, 100, 10, method=LAZY, workspace=at, workspace_bytes=need.value))
+result.append(mallocs.value - before)
+result.append(h.simulate(net, 100, 10, mapping=WAVE))      # needs the records
+limit.value = 1 << 60
+result.append(h.simulate(net, 100, 10, mapping=WAVE))
+result.append(h.lib.rtssa_network_destroy(net))
+""")
+    assert got == [0, 0, 0, 0, -4, 0, 0]
+
+
 @pytest.mark.parametrize("M", [9, 200, 512])
 def test_subwave_rows_are_one_allocation_and_one_copy(fake_hip, M):
     assert _child(fake_hip, """
