@@ -25,7 +25,8 @@ enum { RT_H_ZERO = 0, RT_H_ONE = 1, RT_H_PAIR = 2, RT_H_TWO = 3 };
 struct rt_net_dev {
     int32_t N, M;
     const int2* react;       // [M]
-    const double* c;         // [M]
+    const double* c;         // [M], then (at max(M, 1)) the scale that brings the rates
+                             // into the binary32 order's range
     const int32_t* nu_ptr;   // [M+1] net change v_k as (species, delta) lists
     const int32_t* nu_sp;
     const int32_t* nu_dl;
@@ -33,7 +34,8 @@ struct rt_net_dev {
     const int32_t* dep_idx;
     const int32_t* nu_dense; // [M][N], only for networks of the thread mapping
     // piecewise-constant rates: c applies on [0, sched_t[0]); row i of
-    // sched_c ([B][M]) from sched_t[i] on (sched_B = 0: constant rates)
+    // sched_c ([B][M], then a scale for each piece as after c) from sched_t[i] on
+    // (sched_B = 0: constant rates)
     int32_t sched_B;
     const double* sched_t;
     const double* sched_c;

@@ -64,6 +64,7 @@ struct g2_shared {
     g2_part part[2][16];                 // per firing parity, per wavefront
     rt_sel_part exact[2][16];            // the same for the exact selection
     unsigned long long next_traj;
+    double scale[16];                    // of the rates in force, per wavefront
     uint32_t log_scratch[16][RT_LOG_SCRATCH];
 };
 
@@ -148,7 +149,12 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
             Xb[Npad + j] = v;
         }
         __syncthreads();
-        bool plain = true;
+        // 1/a_k is kept of the scaled a_k.  (The scale is read back from LDS at each
+        // firing, off its chain: from scalar registers, of which the loop spills a
+        // hundred, 1000 species, 4000 channels took 4 % longer.)
+        bool low = false;            // some scaled rate is still below the order's range
+        const double scale = crate[max(M, 1)];
+        sh.scale[wave] = scale;
 #pragma unroll 1
         for (int s1 = 0; s1 < S; ++s1) {
             const int k = tid + s1 * L;
@@ -158,7 +164,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
             if (live) {
                 const double c = crate[k];
                 an = rt_propensity_mem(react[k], c, Xb);
-                plain = plain && rt_plain_rate(c);
+                low = low || (c != 0.0 && c * scale < 0x1p-100);
                 const rt_u4 w =
                     rt_philox4x32_10<false>(rt_u4{0u, (uint32_t)k, traj, net_id}, key0, key1);
                 m0 = (((uint64_t)w.y << 32) | w.x) >> 11;
@@ -171,7 +177,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
             const double p1 = rt_mark_draw(e1, acc);
             const double p0 = live ? e0 : __builtin_inf();
             pa[k] = an;
-            pinv[k] = __builtin_amdgcn_rcpf((float)an);
+            pinv[k] = __builtin_amdgcn_rcpf((float)(an * scale));
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 P[s] = s == s1 ? p0 : P[s];
@@ -188,8 +194,8 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
         unsigned long long hash = kFnvOffset;
         int st = RTSSA_TRAJ_OK;
         uint32_t reduces = 0;        // parity picks the selection's LDS buffer
-        // the smallest gap the binary32 order takes
-        float g_min = __syncthreads_or(!plain) ? __builtin_inff() : 1e-30f;
+        // the smallest gap, over the scale, that the binary32 order takes
+        float g_min = __syncthreads_or(low) ? __builtin_inff() : 1e-30f;
 
         for (;;) {
             // ---- pass: the gaps (P_k - T_k) / a_k in binary32 as keys, the
@@ -255,11 +261,8 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                 int ks = 0;
 #pragma unroll 1
                 for (int s = 0; s < S; ++s) {
-                    double df = 0.0;
-#pragma unroll
-                    for (int q = 0; q < S; ++q) df = q == s ? P[q] - T[q] : df;
                     const double a = pa[tid + s * L];
-                    const double raw = df * (1.0 / a);
+                    const double raw = (P[s] - T[s]) * rt_recip(a);
                     const double e = a == 0.0 ? __builtin_inf() : fmax(raw, 0.0);
                     const bool lt = e < e1;
                     e2 = fmin(e2, fmax(e1, e));
@@ -305,9 +308,11 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                 for (int s = 0; s < S; ++s) T[s] = fma(pa[tid + s * L], db, T[s]);
                 t = b_next;
                 crate = rt_const(net.sched_c) + (size_t)piece * M;
+                const double scale = rt_const(net.sched_c)[(size_t)sB * M + piece];
+                sh.scale[wave] = scale;
                 ++piece;
                 b_next = piece < sB ? rt_const(net.sched_t)[piece] : __builtin_inf();
-                bool ok_rates = true;
+                bool low_rates = false;
 #pragma unroll 1
                 for (int s1 = 0; s1 < S; ++s1) {
                     const int k = tid + s1 * L;
@@ -315,11 +320,11 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                         const double c = crate[k];
                         const double an = rt_propensity_mem(react[k], c, Xc);
                         pa[k] = an;
-                        pinv[k] = __builtin_amdgcn_rcpf((float)an);
-                        ok_rates = ok_rates && rt_plain_rate(c);
+                        pinv[k] = __builtin_amdgcn_rcpf((float)(an * scale));
+                        low_rates = low_rates || (c != 0.0 && c * scale < 0x1p-100);
                     }
                 }
-                g_min = __syncthreads_or(!ok_rates) ? __builtin_inff() : 1e-30f;
+                g_min = __syncthreads_or(low_rates) ? __builtin_inff() : 1e-30f;
                 continue;
             }
             if (d1 == __builtin_inf()) { st = RTSSA_TRAJ_ABSORBED; break; }
@@ -438,7 +443,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                     if (kind == RT_H_TWO) v1 = Xc[s1] + dd.y;
                     const double an = rt_propensity_counts(kind, (uint32_t)v0, (uint32_t)v1, cr);
                     pa[kd] = an;
-                    pinv[kd] = __builtin_amdgcn_rcpf((float)an);
+                    pinv[kd] = __builtin_amdgcn_rcpf((float)(an * sh.scale[wave]));
                 }
                 if (n_other > 63) {
                     // the rest of D(mu) from its 64th other channel on
@@ -452,7 +457,7 @@ __global__ __launch_bounds__(L, g2_min_waves(S)) void rt_group_lds_kernel(rt_cla
                                                             r2.x & RT_SPECIES_MASK, r2.y,
                                                             crate[k2], xnew);
                             pa[k2] = an;
-                            pinv[k2] = __builtin_amdgcn_rcpf((float)an);
+                            pinv[k2] = __builtin_amdgcn_rcpf((float)(an * sh.scale[wave]));
                         }
                     }
                 }

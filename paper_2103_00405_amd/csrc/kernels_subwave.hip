@@ -160,7 +160,7 @@ __global__ __launch_bounds__(block_of(S), subwave_min_waves(S)) void rt_subwave_
 #pragma unroll
                 for (int s = 0; s < S; ++s) {
                     const double a = la[s * 64];
-                    const double raw = df[s] * (1.0 / a);
+                    const double raw = df[s] * rt_recip(a);
                     rt_min2_push(loc, a == 0.0 ? __builtin_inf() : fmax(raw, 0.0), s);
                 }
                 loc = rt_min2_slot_to_channel(loc, li, LOG2L);
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(block_of(S), subwave_min_waves(S)) void rt_subwave_
                 if (d1 == 0.0 && li == (mu & (L - 1))) {
 #pragma unroll
                     for (int s = 0; s < S; ++s)
-                        if ((mu >> LOG2L) == s) clamped = df[s] * (1.0 / la[s * 64]) < 0.0;
+                        if ((mu >> LOG2L) == s) clamped = df[s] * rt_recip(la[s * 64]) < 0.0;
                 }
             }
         }

@@ -426,7 +426,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                     rt_min2 sel{__builtin_inf(), __builtin_inf(), 0};
 #pragma unroll
                     for (int k = 0; k < MT; ++k) {
-                        const double raw = df[k] * (1.0 / a[k]);
+                        const double raw = df[k] * rt_recip(a[k]);
                         rt_min2_push(sel, a[k] == 0.0 ? __builtin_inf() : fmax(raw, 0.0), k);
                     }
                     near = rt_near_tie(sel.d1, sel.d2);
@@ -437,7 +437,7 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
                         // (a clamped gap fires at once; when every channel is
                         // frozen the winner's reciprocal gives d1 = NaN)
                         const bool neg = sel.k == k && a[k] != 0.0 && df[k] < 0.0;
-                        clamped = clamped || (neg && df[k] * (1.0 / a[k]) < 0.0);
+                        clamped = clamped || (neg && df[k] * rt_recip(a[k]) < 0.0);
                         df[k] = neg ? 0.0 : df[k];
                     }
                 }

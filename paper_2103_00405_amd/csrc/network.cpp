@@ -24,6 +24,20 @@ static int validate_rate(double c, int k)
     return RTSSA_OK;
 }
 
+// The power of two that brings the rates into the range in which gaps are ordered
+// in binary32 (rt_plain_rate): 1 where they all are in it, else the largest to
+// [1, 2).  Kept past the last rate of a table.
+static double rate_scale(const double* c, int M)
+{
+    double top = 0.0;
+    bool plain = true;
+    for (int k = 0; k < M; ++k) {
+        top = std::max(top, c[k]);
+        plain = plain && (c[k] == 0.0 || (c[k] >= 0x1p-100 && c[k] <= 0x1p60));
+    }
+    return plain ? 1.0 : ldexp(1.0, -ilogb(top));
+}
+
 static int upload(rtssa_network* n)
 {
     // one device allocation; each table 256-byte aligned
@@ -90,7 +104,7 @@ extern "C" int rtssa_network_create(int32_t N, int32_t M, const int32_t* react_p
     n->N = N;
     n->M = M;
     n->react.resize(std::max(M, 1));
-    n->c.assign(std::max(M, 1), 0.0);
+    n->c.assign(std::max(M, 1) + 1, 0.0);
     n->nu_ptr.assign(M + 1, 0);
     std::vector<std::vector<int>> readers(N);   // species -> channels reading it
     std::vector<std::vector<std::pair<int, int>>> nu(M);
@@ -142,6 +156,7 @@ extern "C" int rtssa_network_create(int32_t N, int32_t M, const int32_t* react_p
         for (auto& kv : delta)
             if (kv.second != 0) nu[k].push_back(kv);
     }
+    n->c.back() = rate_scale(n->c.data(), M);
     if (M == 0) n->react[0] = make_int2(0, 0);
     // net change lists
     for (int k = 0; k < M; ++k) {
@@ -397,7 +412,8 @@ extern "C" int rtssa_network_set_rates(rtssa_network* net, const double* c)
         if (rc) return rc;
     }
     for (int k = 0; k < net->M; ++k) net->c[k] = c[k];
-    const size_t bytes = sizeof(double) * net->M;
+    net->c.back() = rate_scale(net->c.data(), net->M);
+    const size_t bytes = sizeof(double) * net->c.size();
     if (net->group_block && net->M > 0) {
         // the dependency records carry each channel's rate: rewrite those in
         // place (their address may be held by a batch).  Both copies are on the
@@ -448,11 +464,15 @@ extern "C" int rtssa_network_set_schedule(rtssa_network* net, int32_t B, const d
     void* blk = nullptr;
     if (B > 0) {
         const size_t tb = (size_t)B * sizeof(double), cb = (size_t)B * net->M * sizeof(double);
+        std::vector<double> scales(B);
+        for (int32_t i = 0; i < B; ++i) scales[i] = rate_scale(rates + (size_t)i * net->M, net->M);
         const size_t toff = 0, coff = (tb + 255) / 256 * 256;
-        if (hipMalloc(&blk, coff + cb + 256) != hipSuccess)
+        if (hipMalloc(&blk, coff + cb + tb + 256) != hipSuccess)
             return rt_fail(RTSSA_E_NOMEM, "device allocation of the schedule failed");
         if (hipMemcpy((char*)blk + toff, times, tb, hipMemcpyHostToDevice) != hipSuccess ||
-            (cb && hipMemcpy((char*)blk + coff, rates, cb, hipMemcpyHostToDevice) != hipSuccess)) {
+            (cb && hipMemcpy((char*)blk + coff, rates, cb, hipMemcpyHostToDevice) != hipSuccess) ||
+            hipMemcpy((char*)blk + coff + cb, scales.data(), tb, hipMemcpyHostToDevice) !=
+                hipSuccess) {
             hipFree(blk);
             return rt_fail(RTSSA_E_HIP, "copy of the schedule failed");
         }

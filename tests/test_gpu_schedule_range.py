@@ -88,3 +88,32 @@ def test_rates_leave_the_binary32_range_and_return(M, mapping, block):
     ref = _compare(spec, x0, t_end, _range_schedule(spec, t_end), 24, 9, mapping=mapping,
                    block=block)
     assert ref["stats"]["firings"] > 24 * 100
+
+
+@pytest.mark.parametrize("f", [1e-40, 1e-150, 1e40])
+def test_rates_set_later_are_ordered_by_their_own_scale(f):
+    """set_rates moves a workgroup-mapping network out of the binary32 range and
+    back, alone and under a batch that was made before."""
+    from paper_2103_00405_amd import api
+    spec, x0, t_end = _net(700, 901, 300)
+    c = np.asarray(spec.c)
+    net = api.Network(spec)
+    job = dict(net=net, x0=x0, t_end=t_end / f, sample_t=[t_end / f], R=8, net_id=0)
+    batch = api.Batch([job], max_firings=2000, with_hash=True)
+    for scale in (f, 1.0, f):
+        net.set_rates(c * scale)
+        batch.run(seed=5)
+        g = api.simulate(net, x0, t_end / f, [t_end / f], 8, seed=5, with_hash=True,
+                         max_firings=2000)
+        torch.cuda.synchronize()
+        if scale != f:
+            continue
+        ref = oracle.simulate(W.with_rates(spec, c * scale), x0, t_end / f, [t_end / f], 5, 8,
+                              max_firings=2000)
+        for key, view in KEYS:
+            for out in (g, batch.outputs[0]):
+                got, want = out[key].cpu().numpy(), ref[key]
+                if view is not None:
+                    got, want = got.view(view), want.view(view)
+                assert np.array_equal(got, want), key
+    batch.close()
