@@ -48,14 +48,14 @@
 
 namespace {
 
-// Threads of a workgroup, which shares one 6 KiB logarithm table: the size that
-// leaves a CU's LDS the most wavefronts (10 at 8 slots, 12 at 6, 16 below).
-constexpr int block_of(int S) { return S >= 8 ? 128 : 256; }
+// Wavefronts of a workgroup, which share one 6 KiB logarithm table, at most.
+constexpr int kWaves = 4;
 
 // Draws are made once this many lanes of a wavefront wait for one.
 constexpr int kDrawLanes = 16;
 
-// Waves per SIMD the register allocation must allow (no more fit in LDS).
+// Waves per SIMD the register allocation must allow (no more fit in LDS: 10 a CU
+// at 8 slots, 12 at 6, 16 below).
 constexpr int subwave_min_waves(int S) { return S <= 5 ? 4 : 3; }
 
 // LDS bytes of one wavefront: per slot and lane a_k, the next draw, 1 / a_k
@@ -66,9 +66,8 @@ constexpr size_t wave_lds_bytes(int L, int S, int NP)
 }
 
 template <int L, int S, bool SCHED>
-__global__ __launch_bounds__(block_of(S), subwave_min_waves(S)) void rt_subwave_kernel(rt_class_dev C)
+__global__ __launch_bounds__(64 * kWaves, subwave_min_waves(S)) void rt_subwave_kernel(rt_class_dev C)
 {
-    constexpr int kBlock = block_of(S);
     constexpr int G = 64 / L;                              // groups of a wavefront
     constexpr int LOG2L = __builtin_ctz(L);
     constexpr int32_t kKey = 8 * L - 1;                    // channel bits of a selection key
@@ -81,9 +80,9 @@ __global__ __launch_bounds__(block_of(S), subwave_min_waves(S)) void rt_subwave_
     const int tid = threadIdx.x, lane = tid & 63, li = lane % L, gbase = lane - li;
     const unsigned long long gmask = kGroupBits << gbase;
     extern __shared__ __align__(16) char dyn_lds[];
-    __shared__ rt_log_lds<kBlock / 64> log_lds;
+    __shared__ rt_log_lds<kWaves> log_lds;
     const auto sc = log_lds.init();
-    __shared__ rt_wave_share wave_shares[kBlock / 64];
+    __shared__ rt_wave_share wave_shares[kWaves];
     rt_wave_share& share = wave_shares[tid >> 6];
     share.clear();
     share.start_item(false);
@@ -478,21 +477,20 @@ int rt_subwave_slots(int M, int L)
     return s <= 2 ? 2 : (s <= 4 ? 4 : (s <= 6 ? s : (s <= 8 ? 8 : 0)));
 }
 
-// LDS bytes of a workgroup: the dynamic part the launch asks for, and with the
-// logarithm table and the wavefronts' shares.
-static size_t dynamic_lds_bytes(int L, int S, int N)
+// LDS bytes of a workgroup of `waves` wavefronts: the dynamic part the launch asks
+// for, and with the logarithm table and the wavefronts' shares.
+static size_t dynamic_lds_bytes(int waves, int L, int S, int N)
 {
-    return (size_t)(block_of(S) / 64) * wave_lds_bytes(L, S, (N + 3) & ~3);
+    return waves * wave_lds_bytes(L, S, (N + 3) & ~3);
 }
 
-static size_t group_lds_bytes(int L, int S, int N)
+static size_t group_lds_bytes(int waves, int L, int S, int N)
 {
-    const size_t fixed = block_of(S) == 128 ? sizeof(rt_log_lds<2>) + 2 * sizeof(rt_wave_share)
-                                            : sizeof(rt_log_lds<4>) + 4 * sizeof(rt_wave_share);
-    return (fixed + 15) / 16 * 16 + dynamic_lds_bytes(L, S, N);
+    constexpr size_t fixed = sizeof(rt_log_lds<kWaves>) + kWaves * sizeof(rt_wave_share);
+    return (fixed + 15) / 16 * 16 + dynamic_lds_bytes(waves, L, S, N);
 }
 
-// A workgroup's LDS limit (0: no device answers).
+// A workgroup's LDS limit, which is also a CU's LDS (0: no device answers).
 static size_t lds_limit()
 {
     int dev = 0, bytes = 0;
@@ -502,18 +500,42 @@ static size_t lds_limit()
     return (size_t)bytes;
 }
 
-// Whether L lanes a trajectory leave room for N species beside any network of
-// M's slot range (a batch's class runs its networks with the most slots of one
-// and the most species of another).  A launch that fits at L fits at 2 L.
+// Wavefronts per workgroup: the number that leaves a CU's LDS the most wavefronts
+// (0: not one fits), the larger of equals; *cu: that most.  2 at 8 slots and 4
+// below while the counts X are small beside the channels' state; fixed at those,
+// networks of many species lost to idle SIMDs (16000 trajectories: 250 channels,
+// 1500 species 17.1 ms, 11.5 this way; 400, 3000 31.0 and 20.7; 128, 800 8.3 and
+// 5.5).
+static int group_waves(size_t limit, int L, int S, int N, int* cu)
+{
+    int best = 0;
+    *cu = 0;
+    for (int w = kWaves; w >= 1; --w) {
+        const int n = std::min(w * (int)(limit / group_lds_bytes(w, L, S, N)),
+                               4 * subwave_min_waves(S));
+        if (n > *cu) {
+            *cu = n;
+            best = w;
+        }
+    }
+    return best;
+}
+
+// Whether L lanes a trajectory leave every SIMD of a CU a wavefront beside N
+// species, for any network of M's slot range (a batch's class runs its networks
+// with the most slots of one and the most species of another).  More lanes are
+// more wavefronts of fewer trajectories, about as many trajectories in all.
 bool rt_subwave_fits(int M, int N, int L)
 {
+    int cu = 0;
     const size_t limit = lds_limit();
-    return limit == 0 || group_lds_bytes(L, rt_subwave_slots(M, L) <= 4 ? 4 : 6, N) <= limit;
+    if (limit) group_waves(limit, L, rt_subwave_slots(M, L) <= 4 ? 4 : 8, N, &cu);
+    return limit == 0 || cu >= 4;
 }
 
 // Lanes per trajectory when nothing else says: as many as keep the units'
 // wavefronts within waves_per_cu, at least 8 and rt_subwave_lanes, and as many
-// as the species need to fit (whether a network runs does not depend on the
+// as the species call for (so whether a network runs does not depend on the
 // units).  More lanes are fewer slots and fewer groups a wavefront, so a faster
 // firing, while a wavefront has its SIMD to itself; on a full device fewer lanes
 // do more per instruction (45 channels, lanes 8 / 16 / 32 / 64: 300 trajectories 3.7 / 2.8
@@ -539,10 +561,11 @@ int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStre
     if (!kfn) return rt_fail(RTSSA_E_UNSUPPORTED, "no sub-wave kernel for this size");
     const size_t limit = lds_limit();
     if (limit == 0) return rt_fail(RTSSA_E_HIP, "device query failed");
-    if (group_lds_bytes(L, S, C.max_N) > limit)
-        return rt_fail(RTSSA_E_UNSUPPORTED, "sub-wave LDS too large");
-    const int kBlock = block_of(S);
-    const size_t lds = dynamic_lds_bytes(L, S, C.max_N);
+    int cu_waves = 0;
+    const int waves = group_waves(limit, L, S, C.max_N, &cu_waves);
+    if (waves == 0) return rt_fail(RTSSA_E_UNSUPPORTED, "sub-wave LDS too large");
+    const int block = 64 * waves;
+    const size_t lds = dynamic_lds_bytes(waves, L, S, C.max_N);
     if (lds > 48 * 1024 &&
         hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)
@@ -552,13 +575,13 @@ int rt_launch_subwave(int max_M, const rt_class_dev& C, int L, int grid, hipStre
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return rt_fail(RTSSA_E_HIP, "device query failed");
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, kBlock, lds) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, block, lds) != hipSuccess ||
             per_cu < 1)
             per_cu = 1;
         grid = cus * per_cu;
     }
     if (grid_used) *grid_used = grid;
-    hipLaunchKernelGGL(kfn, dim3(grid), dim3(kBlock), lds, stream, C);
+    hipLaunchKernelGGL(kfn, dim3(grid), dim3(block), lds, stream, C);
     return hipGetLastError() == hipSuccess ? RTSSA_OK
                                            : rt_fail(RTSSA_E_HIP, "sub-wave kernel launch failed");
 }

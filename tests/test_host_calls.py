@@ -124,8 +124,8 @@ result = [h.batch(nets, R) for R in (1, 10, 100, 1000, 10000)]
 
 def test_subwave_refuses_species_past_the_lds(fake_hip):
     assert _child(fake_hip, """
-net = h.network(64, 12000)
-result = [(h.simulate(net, 12000, R, mapping=WAVE), h.error()) for R in (1, 30000)]
+net = h.network(64, 45000)
+result = [(h.simulate(net, 45000, R, mapping=WAVE), h.error()) for R in (1, 30000)]
 """) == [[-2, "sub-wave LDS too large"]] * 2
 
 
@@ -173,3 +173,14 @@ opt, need = h.types.Options(mapping=WAVE), C.c_size_t()
 result = [h.lib.rtssa_workspace_size(net, 10, C.byref(opt), C.byref(need)),
           h.counter('mallocs').value - mallocs, h.counter('copies').value - copies]
 """ % M) == [0, 1, 1]
+
+
+@pytest.mark.parametrize("M,N,lanes,block", [
+    (64, 16, 8, 128), (60, 15, 8, 128), (48, 12, 8, 256), (40, 10, 8, 256), (301, 75, 64, 256),
+    (64, 400, 8, 192), (250, 1500, 32, 192), (400, 3000, 64, 192), (64, 1900, 8, 128)])
+def test_subwave_workgroups_fill_the_lds(fake_hip, M, N, lanes, block):
+    """Wavefronts per workgroup: the number that leaves a CU the most of them."""
+    assert _child(fake_hip, """
+net = h.network(%d, %d)
+result = [h.simulate(net, %d, 5000, mapping=WAVE, block=%d), h.counter('last_block').value]
+""" % (M, N, N, lanes)) == [0, block]
