@@ -47,16 +47,6 @@ int rt_auto_group_size(int M)
     return 16 * L >= M ? L : 1024;
 }
 
-// Lanes per trajectory of the sub-wave mapping: the requested value, or the
-// fewest lanes holding every channel in at most 8 slots; never fewer lanes
-// than species changed by one reaction.
-int rt_pick_lanes(const rtssa_network* net, int requested)
-{
-    int L = requested > 0 ? requested : rt_subwave_lanes(net->M);
-    while (L < 64 && L < net->max_nu) L <<= 1;
-    return L;
-}
-
 // Launch one class with the given mapping; block = lanes per trajectory for
 // the sub-wave mapping, threads per trajectory for the workgroup mapping,
 // workgroup size for the thread mapping.
