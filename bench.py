@@ -43,7 +43,7 @@ sys.path.insert(0, ROOT)
 ALG_SLOTS_PER_FIRING_LV = 175
 # Instructions the profiler counts per firing of the headline kernel
 # (SQ_INSTS_VALU x 64 / firings; profiles/rt_thread_kernel_lv_ensemble_sq_counters.md).
-ISSUED_VALU_PER_FIRING_LV = 197
+ISSUED_VALU_PER_FIRING_LV = 195
 
 
 # Algorithmic lane-ops of one firing of an M-channel network in the eager
@@ -62,14 +62,14 @@ PEAK_LANE_SLOTS = 256 * 4 * 16 * CLOCK_HZ   # CUs x SIMDs x lanes x clock = 3.93
 # from two rocprofv3 counter passes (FETCH_SIZE, WRITE_SIZE) scaled by the same
 # counters on a 1 GiB copy (factors 2.0 and 1.0).  Valid for the kernel as
 # profiled; set to None when the kernel changes until it is measured again.
-LV_TRAFFIC_BYTES_PER_LAUNCH = 8.341e+09
+LV_TRAFFIC_BYTES_PER_LAUNCH = 1.0065e+10
 
 # VALU instructions (wave64) of one step of the batched workload: SQ_INSTS_VALU
 # summed over the timed replay's eleven class kernels in one rocprofv3 counter
 # pass.  At 4 cycles per instruction on 256 x 4 SIMDs the step cannot take
 # less than this many cycles' worth of issue; valid for the kernels and the
 # autotuner's plan as profiled, None when they change until measured again.
-BATCH_VALU_INSTR_PER_STEP = 4.200e+11
+BATCH_VALU_INSTR_PER_STEP = 4.356e+11
 SIMD_ISSUE_HZ = 256 * 4 * CLOCK_HZ / 4        # wave64 VALU instructions per second
 
 

@@ -119,8 +119,9 @@ typedef struct {
  * is clamped and counted as above); nothing fires at b.  E_UNSUPPORTED when
  * the tree does not fit LDS
  * (about 13,000 channels).  The first LAZY run of a network builds its
- * fixed-stride rows (about 270 bytes per channel of device memory, kept
- * until the network is destroyed); that first run must not overlap another
+ * fixed-stride rows (about 270 bytes per channel of device memory, and 2 KiB
+ * more up to 512 channels where there is memory for them, kept until the network
+ * is destroyed); that first run must not overlap another
  * call on the same network from a second host thread.  Its channel workspace
  * (44 bytes per channel per resident wavefront) is allocated stream-ordered
  * by the call. */
@@ -218,9 +219,10 @@ int rtssa_network_set_schedule(rtssa_network* net, int32_t B, const double* time
  * work-queue heads, plus, for LAZY, one slice of channel records per resident
  * wavefront (about 44 bytes per channel each).  For LAZY, DIRECT_TREE and the
  * random-time sub-wave and workgroup mappings it also builds the network's fixed-stride
- * rows (its jumps and dependency lists, about 256 bytes per channel; for the
- * workgroup mapping also 64 dependency records of 32 bytes per channel) if they
- * are not built yet (synchronous; they are allocated once per network), so
+ * rows (its jumps and dependency lists, about 270 bytes per channel; for the
+ * sub-wave and workgroup mappings, and beside a tree method's rows up to 512
+ * channels, also 64 dependency records of 32 bytes per channel) if they are not
+ * built yet (synchronous; they are allocated once per network), so
  * that a later call with a caller workspace allocates nothing.  No stream
  * work otherwise.
  */
@@ -424,8 +426,11 @@ int32_t rtssa_debug_neglog_quick_host(uint64_t m, double* y);
 /* out[i] = RN(1 / a[i]) as the kernels compute it (device arrays; a and 1 / a
  * normal). */
 int rtssa_debug_recip(const double* a, double* out, int64_t count, rtssa_stream_t stream);
-/* The selection step (Eq. 25) and the near-tie rule of one mapping, run by
- * the same device functions as the simulation kernels on given values:
+/* The exact selection step (Eq. 25) and the near-tie rule of one mapping on
+ * given values, by the same binary64 device functions as the simulation kernels.
+ * The thread, sub-wave and LDS workgroup kernels come to them where two gaps are
+ * too close for their binary32 order, or the smallest is outside its range; that
+ * order itself is not run here:
  * v device float64 [count][M] (no NaN; +inf allowed); per row r:
  * mu[r] = the lowest k among the smallest values, v1[r] that value,
  * v2[r] the second smallest counted with multiplicity (+inf if none),

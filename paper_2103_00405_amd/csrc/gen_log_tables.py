@@ -14,7 +14,7 @@ Tables written here:
   INVK_FIX[j][9]   1/(j+1) in the same format, j = 0..KMAX (Horner for ln(1+z))
   LN2_H, LN2_L     ln 2 split so that e * LN2_H is exact for |e| <= 64
   THIRD_H, THIRD_L 1/3 as a double-double
-First (quick) phase, a table of 256 pairs for the top 8 mantissa bits of f in
+First (quick) phase, a table of 256 triples for the top 8 mantissa bits of f in
 [1, 2), with -ln u = -e ln 2 + ln r - ln(1 + z) and r in [1/2, 1]:
   LOGQ[3 i ..]     (H, L, r_i): H is ln r_i to a multiple of 2^-46, L the rest
   QLN2_H, QLN2_L   ln 2 in the same form: at u just below 1 (r = 1/2, e = -1)

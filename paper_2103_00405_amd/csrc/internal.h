@@ -71,7 +71,8 @@ struct rtssa_network {
     void* dev_block = nullptr;  // one allocation holding every device table
     void* sched_block = nullptr;  // device copy of the rate schedule (times, rates)
     void* lazy_block = nullptr;   // the lazy form's fixed-stride rows
-    void* group_block = nullptr;  // the workgroup mapping's dependency records
+    void* group_block = nullptr;  // the eager mappings' dependency records (the rows
+                                  // too, where lazy_block is the same)
     int32_t batch_refs = 0;       // batch items holding this network's device pointers
     rt_net_dev dev{};
 };
@@ -201,9 +202,8 @@ size_t rt_group_lds2_bytes(int N, int L, int S);
 int rt_launch_group_lds(int M, int max_N, const rt_class_dev& C, int L, int grid,
                         hipStream_t stream, int* grid_used);
 // the fixed-stride rows a run of this network with these options reads:
-// 0 none, 1 the lazy form's rows (tree methods; the random-time sub-wave
-// mapping), 2 those and the workgroup
-// mapping's dependency records (random-time workgroup mapping)
+// 0 none, 1 the rows alone (tree methods), 2 those and the dependency records
+// (random-time sub-wave and workgroup mappings)
 int rt_run_rows(const rtssa_network* net, const rtssa_options& o);
 bool rt_rows_ready(const rtssa_network* net, int rows);
 int rt_rows_prepare(rtssa_network* net, int rows);
@@ -225,7 +225,7 @@ int rt_launch_dmtree(const rt_class_dev& C, int max_N, int max_M, int grid, int6
                      hipStream_t stream, int* grid_used);
 // builds and uploads the lazy form's rows of a network once (network.cpp)
 int rt_lazy_prepare(rtssa_network* net);
-// the same plus the workgroup mapping's dependency records (network.cpp)
+// the same plus the eager mappings' dependency records (network.cpp)
 int rt_group_rows_prepare(rtssa_network* net);
 int rt_subwave_slots(int M, int L);
 int rt_subwave_lanes(int M);

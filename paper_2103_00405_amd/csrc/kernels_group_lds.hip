@@ -6,8 +6,8 @@
 // thread k mod L, slot k / L (slots past M are frozen channels).  Per thread,
 // registers hold each slot's T_k, P_k, the channel's next unit-exponential
 // draw E(k, n_k + 1) (computed ahead, off the firing's critical path) and
-// n_k.  LDS holds a_k and a binary32 1/a_k of every channel and two buffers of
-// the species counts X.
+// n_k.  LDS holds a_k and a binary32 1/a_k (of a_k scaled into binary32's range)
+// of every channel and two buffers of the species counts X.
 //
 // One firing (section 4, Table 2, in the internal-time form of Eq. 14-16):
 //   pass    every thread forms the gaps (P_k - T_k) / a_k of its slots in
@@ -19,7 +19,7 @@
 //           smallest is no plain positive number, the exact binary64 selection
 //           (lowest k wins ties, Eq. 25) behind a second barrier.  Against
 //           binary64 gaps, their second minimum and cached RN(1 / a_k):
-//           1000 species, 4000 channels, 512 trajectories 150.5 -> 124.5 ms
+//           1000 species, 4000 channels, 512 trajectories 150.5 -> 120 ms
 //           (the firing's latency bounds it: 2 wavefronts a SIMD);
 //   event   every wavefront loads mu's fixed-stride rows (its jump v_mu and
 //           the records of the channels D(mu) reading a changed species --

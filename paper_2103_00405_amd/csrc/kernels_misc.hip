@@ -147,8 +147,9 @@ __global__ void rt_debug_recip_kernel(const double* a, double* out, int64_t coun
     if (i < count) out[i] = rt_recip(a[i]);
 }
 
-// ---- the selection step (Eq. 25) and near-tie rule of each mapping, on
-// rows of given values (test hook); the same device functions as the kernels
+// ---- the exact selection (Eq. 25) and near-tie rule of each mapping, on rows of
+// given values (test hook): the binary64 device functions of the register workgroup
+// kernel, and of the others where their binary32 order does not decide
 __device__ __forceinline__ void debug_sel_store(int64_t r, const rt_min2& v, int32_t* mu,
                                                 double* v1, double* v2, uint8_t* near)
 {

@@ -126,7 +126,7 @@ constexpr int kGridLds = 128;
 
 // Waves per SIMD each instantiation is compiled for: the most at which the
 // firing loop's state fits without spilling to scratch (the branches of rare
-// events spill up to 112 bytes, which measured nothing).
+// events spill up to 88 bytes).
 constexpr int thread_min_waves(int MT, int NT, int METHOD, bool SCHED)
 {
     if (METHOD == RTSSA_METHOD_DIRECT) return 4;
@@ -221,11 +221,12 @@ __global__ __launch_bounds__(256, thread_min_waves(MT, NT, METHOD, SCHED)) void 
         const uint32_t net_id = it->net_id, traj_offset = it->traj_offset;
         const bool want_hash = it->seq_hash != nullptr;
         const uint32_t net_k1 = net_id ^ key1;
-        // sample rows: X goes straight to memory at each sample point (through a
-        // 64-byte line buffer per lane HBM saw a sixth of the writes, 1.3 against
-        // 5.4 GB a launch of 2^20 Lotka-Volterra trajectories, but a point cost
-        // three times the instructions and the device writes some 5 GB a second of the
-        // 5 TB/s it can)
+        // sample rows: X goes straight to memory at each sample point.  A 64-byte
+        // line buffer per lane kept the traffic of a launch of 2^20 Lotka-Volterra
+        // trajectories at 1.3 GB, where it is 10.1, but a point cost three times the
+        // instructions, and 10.1 GB in 0.78 s are 0.3 % of what the card moves.
+        // Grids of 10000 points with some 300 firings: 256 trajectories 40.5 ms in
+        // the kernel with the buffer, 3.6 without; 40000 trajectories 41.9 and 13.1.
         int32_t* const samples = it->samples;
         const int32_t G = it->G;
         const int64_t ss_n = it->ss_n, ss_g = it->ss_g;
@@ -740,11 +741,12 @@ int launch_mn(rt_class_dev C, int* block, int grid, hipStream_t stream, int* gri
             // A small ensemble: single wavefronts of few lanes on three quarters
             // of the CUs.  A firing's latency bounds it, and a wavefront waits
             // for every lane's rare events, so fewer lanes are faster while each
-            // wavefront has its CU to itself (Lotka-Volterra, 256 / 1000 / 2000
-            // trajectories: 7.0 / 7.0 / 3.8 ms in workgroups of 256 full lanes,
-            // 4.7 / 5.1 / 3.2 ms at 2, 6 and 11 lanes; 8.8 ms for 1000 one-lane
-            // wavefronts, four to a CU; from 8000 trajectories on full
-            // wavefronts are as fast).
+            // wavefront has its CU to itself (Lotka-Volterra from 100, 100 to t = 5,
+            // workgroups of 256 full lanes against few lanes: 64 trajectories 1.68
+            // and 1.12 ms, 256 1.76 and 1.19, 1000 1.89 and 1.38, 1536 1.93 and
+            // 1.47).  The line at 6 a CU is not where few lanes stop being faster:
+            // beyond it they measured 1.53 ms for 1.93 at 2000 trajectories, 1.69
+            // for 1.95 at 4000, 1.72 for 1.97 at 8000, the same from 16000 on.
             *block = 64;
             C.lanes = (int32_t)std::max<int64_t>(1, (4 * lanes_wanted + 3 * cus - 1) / (3 * cus));
         }

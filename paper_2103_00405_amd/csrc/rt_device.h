@@ -170,8 +170,9 @@ __device__ __forceinline__ unsigned long long rt_first_lane_u64(unsigned long lo
 // One wavefront's share of the trajectory counter and of the run's counts, in
 // LDS.  Lanes take trajectories from the reserved range [next, end); when a
 // pass needs more than are left, one lane reserves as many as the stopping
-// lanes need, and more while many trajectories are left (a quarter of an even
-// share of the rest, at most 64).  Firings and end states are summed here and
+// lanes need, and more while many trajectories are left: a quarter of an even
+// share, at most 64, of what was left when this wavefront last reserved (others
+// have taken some since, so near the end it may take more than a quarter).  Firings and end states are summed here and
 // added to the run's counters once, when the wavefront ends.  With one
 // device-wide atomic per trajectory for the trajectory and two for the counts,
 // all on one line, ensembles of short trajectories were bound by those: the

@@ -304,7 +304,7 @@ RT_HD bool rt_rounding_certain(double yh, double yl)
     return yl + err < half_up && yl - err > -half_dn;
 }
 
-// Quick phase, ahead of the fast one: one 16-byte table read and 27 binary64
+// Quick phase, ahead of the fast one: one 24-byte table read and 27 binary64
 // operations decide all but about one draw in 2^12.5; the rest take the fast
 // phase (twice the operations, three table reads and a longer test).
 // u = (m + 1) 2^-53 = 2^e f, f in [1, 2); z = f r - 1 exactly (r has 9
