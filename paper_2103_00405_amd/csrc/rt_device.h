@@ -172,13 +172,14 @@ __device__ __forceinline__ unsigned long long rt_first_lane_u64(unsigned long lo
 // pass needs more than are left, one lane reserves as many as the stopping
 // lanes need, and more while many trajectories are left: a quarter of an even
 // share, at most 64, of what was left when this wavefront last reserved (others
-// have taken some since, so near the end it may take more than a quarter).  Firings and end states are summed here and
-// added to the run's counters once, when the wavefront ends.  With one
-// device-wide atomic per trajectory for the trajectory and two for the counts,
-// all on one line, ensembles of short trajectories were bound by those: the
-// expectation and gradient of a birth-death process over 2^18 trajectories of
-// 200 firings took 5.73 ms, 2.25 ms with the reservations and 0.84 ms with no
-// atomic made past the last trajectory.
+// have taken some since, so near the end it may take more than a quarter).
+// Firings and end states are summed here and added to the run's counters once,
+// when the wavefront ends.  With one device-wide atomic per trajectory for the
+// trajectory and two for the counts, all on one line, ensembles of short
+// trajectories were bound by those: the expectation and gradient of a birth-
+// death process over 2^18 trajectories of 200 firings took 5.73 ms, 2.25 ms
+// with the reservations and 0.84 ms with no atomic made past the last
+// trajectory.
 struct rt_wave_share {
     int64_t next, end;
     unsigned long long firings;
